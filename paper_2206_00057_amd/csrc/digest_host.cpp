@@ -225,6 +225,46 @@ int32_t build_blocks(const std::vector<int32_t> &rowptr, int32_t n_rows,
     return n_long;
 }
 
+// Blocks of a sliced aggregation (launch_spmm_slice): rows of more than
+// kSliceLong entries get a workgroup each, the others form strips of
+// consecutive rows with about 1 / kSliceStrips of the CSR's work, a wave
+// each; both by descending entry count, so that the waves of a workgroup end
+// together and the longest start first.  Returns the number of long rows.
+constexpr int32_t kSliceLong = 2048;
+constexpr int64_t kSliceStrips = 4096;
+constexpr int64_t kSliceRowCost = 32;   // a row's own cost, in entries
+
+int32_t build_slice_blocks(const int32_t *rowptr, int32_t n_rows, std::vector<SpmmBlock> &blocks)
+{
+    const int64_t total = rowptr[n_rows] - rowptr[0] + kSliceRowCost * n_rows;
+    const int64_t target = std::max<int64_t>(256, total / kSliceStrips);
+    std::vector<SpmmBlock> strips;
+    blocks.clear();
+    for (int32_t r = 0; r < n_rows;) {
+        if (rowptr[r + 1] - rowptr[r] > kSliceLong) {
+            blocks.push_back({r, 0, rowptr[r], rowptr[r + 1]});
+            ++r;
+            continue;
+        }
+        const int32_t first = r;
+        int64_t work = 0;
+        while (r < n_rows && rowptr[r + 1] - rowptr[r] <= kSliceLong &&
+               (r == first || work + rowptr[r + 1] - rowptr[r] + kSliceRowCost <= target)) {
+            work += rowptr[r + 1] - rowptr[r] + kSliceRowCost;
+            ++r;
+        }
+        strips.push_back({first, r - first, rowptr[first], rowptr[r]});
+    }
+    auto longer = [](const SpmmBlock &a, const SpmmBlock &b) {
+        return a.ke - a.kb > b.ke - b.kb;
+    };
+    std::stable_sort(blocks.begin(), blocks.end(), longer);
+    std::stable_sort(strips.begin(), strips.end(), longer);
+    const int32_t n_long = (int32_t)blocks.size();
+    blocks.insert(blocks.end(), strips.begin(), strips.end());
+    return n_long;
+}
+
 // A tiered plan of one aggregation (one sparse operand at one width).  The
 // source rows (columns of the operand) are ranked by how many entries read
 // them; tier t holds the rows ranked [t H, (t+1) H), where H rows of one
@@ -415,6 +455,10 @@ struct digest_partition {
     // longest first measured 10-13 us slower on the OGB-Products-shaped
     // 48-float layer)
     std::vector<SpmmBlock> blocks_s_rows, blocks_t_rows;
+    // P_s and P_in^T for the aggregations out of an XCD's L2 (empty where
+    // sliced_pays says no)
+    std::vector<SpmmBlock> blocks_s_slice, blocks_t_slice;
+    int32_t long_s_slice = 0, long_t_slice = 0;
     // DIGEST_PULL_ROWS: a pull fills the halo buffer, then S from it;
     // DIGEST_PULL_AGGREGATE: a pull forms S straight from the store and
     // leaves the halo buffer alone (the calls that read it refuse).
@@ -438,7 +482,8 @@ struct digest_partition {
         size_t rowptr, col, val, t_rowptr, t_src, t_val, halo_gid, bnd_local, bnd_gid, owned_gid;
         size_t blocks_f, blocks_t, blocks_tf, blocks_th;
         size_t s_rowptr, s_col, s_val, b_rowptr, b_col, b_gcol, b_val, blocks_s, blocks_b;
-        size_t blocks_s_rows, blocks_t_rows;
+        size_t blocks_s_rows, blocks_t_rows, blocks_s_slice, blocks_t_slice;
+        size_t slices;                  // a sliced aggregation's source in column slices
         size_t fuse_order, fuse_order_t;   // per owned row, uint8 (see fuse_order below)
         size_t fz;                      // the fused input gradient's D and long rows
         size_t wt;                      // W^T of the fused input gradient
@@ -593,6 +638,36 @@ TfPlan tf_plan(int64_t n_own, int64_t n2, int64_t d_in, int64_t d_out)
     return t;
 }
 
+// Whether the aggregations of rows of d floats over P_s and P_in^T run out of
+// the XCDs' L2s (launch_spmm_slice) instead of gathering whole rows past
+// them.  The lines, by measured layer times (whole rows / sliced, us):
+//   rows: 128-byte slices of 32,768 rows fill one 4 MiB L2.  Twice as many
+//     still pay, the rows read often staying in it (60,000 rows of 256
+//     floats, lognormal mean 83: 736 / 542); at 150,000 rows they no longer
+//     do (mean 48: 1,108 / 1,229).
+//   entries per row: a slice costs each row its own fixed work, and the
+//     source is laid out once (29,125 rows of 256 floats, mean 8: 105 / 114,
+//     mean 12, Zipf: 215 / 119; 60,000 rows, mean 12: 211 / 250, mean 24,
+//     Zipf: 472 / 284).
+//   source bytes: a source of up to about 6 MB is read out of the L2s anyway
+//     (4,000 rows of 256 floats: 154 / 171, 8,000: 270 / 213).
+//   rows of at most 64 floats: their whole-row kernel is a lane group per
+//     row, which needs more rows and entries to lose (41 floats: 8,000 rows
+//     of mean 625 84 / 71, 29,125 rows of mean 24 26 / 29, mean 32 35 / 32).
+constexpr int64_t kSliceMaxRows = 65536;
+constexpr int32_t kSliceMinWidth = 40;
+
+bool sliced_pays(const digest_partition &p, int32_t d)
+{
+    const int64_t n = p.n_own;
+    const bool narrow = d <= digest::kNarrowWide;
+    if (d < kSliceMinWidth || n > kSliceMaxRows)
+        return false;
+    if (narrow ? n < 8000 : n * d * 4 < 6000000)
+        return false;
+    return p.nnz_in >= n * std::max<int64_t>(narrow ? 32 : 12, n / 2500);
+}
+
 void plan_layout(digest_partition &p)
 {
     auto &l = p.lay;
@@ -628,6 +703,8 @@ void plan_layout(digest_partition &p)
     l.blocks_s = take(sizeof(SpmmBlock) * p.blocks_s.size());
     l.blocks_s_rows = take(sizeof(SpmmBlock) * p.blocks_s_rows.size());
     l.blocks_t_rows = take(sizeof(SpmmBlock) * p.blocks_t_rows.size());
+    l.blocks_s_slice = take(sizeof(SpmmBlock) * p.blocks_s_slice.size());
+    l.blocks_t_slice = take(sizeof(SpmmBlock) * p.blocks_t_slice.size());
     l.blocks_b = take(sizeof(SpmmBlock) * p.blocks_b.size());
     l.halo_buf.assign(p.L, 0);
     l.hagg.assign(p.L, 0);
@@ -676,6 +753,12 @@ void plan_layout(digest_partition &p)
             fz = std::max<int64_t>(fz, 2 * (int64_t)p.n_own * padded_width(p.widths[k]));
             wt = std::max<int64_t>(wt, (int64_t)p.widths[k - 1] * p.widths[k]);
         }
+    int64_t slices = 0;
+    for (int32_t k = 0; k <= p.L; ++k)
+        if (sliced_pays(p, p.widths[k]))
+            slices = std::max<int64_t>(slices, ((int64_t)p.n_own + p.n_bnd) *
+                                                   ((p.widths[k] + 31) / 32 * 32));
+    l.slices = take(sizeof(float) * (size_t)slices);
     l.fz = take(sizeof(float) * (size_t)fz);
     l.wt = take(sizeof(float) * (size_t)wt);
     l.tmp = take(sizeof(float) * (size_t)p.n_own * wmax);
@@ -915,7 +998,7 @@ bool fuse_backward(const digest_partition &p, int32_t layer, bool transform_firs
     const int64_t mode = env_int("DIGEST_FUSE", 1);
     if (mode == 0 || transform_first || layer < 2 || layer >= p.L || p.n_own <= 0 ||
         d_out < digest::kFuseMinWidth || d_out > digest::kFuseMaxWidth ||
-        (mode == 1 && p.n_own < kFuseMinRows))
+        (mode == 1 && (p.n_own < kFuseMinRows || sliced_pays(p, p.widths[layer - 1]))))
         return false;
     return find_tiers(p, Csr::InT, p.widths[layer - 1]) == nullptr;
 }
@@ -929,9 +1012,36 @@ bool fuse_forward(const digest_partition &p, int32_t layer, bool transform_first
     // layer took 557 + 696 us fused against 1,087 + 70 us
     if (mode == 0 || transform_first || p.n_own <= 0 || narrow_out(d_in, d_out) ||
         d_in < digest::kFuseMinWidth || d_in > digest::kFuseMaxWidth ||
-        (mode == 1 && p.n_own < kFuseMinRows))
+        (mode == 1 && (p.n_own < kFuseMinRows || sliced_pays(p, d_in))))
         return false;
     return find_tiers(p, Csr::InH, padded_width(d_in)) == nullptr;
+}
+
+// The aggregation over P_s (InH) or P_in^T (InT) out of the XCDs' L2s: the
+// n_own rows of src0 (d floats, row stride ld0; masked by mask > 0, row
+// stride ldm, if given) laid out in column slices, then gathered slice by
+// slice; P_s's halo-aggregate entries read the rows of src1 (row stride ld1).
+digest_status run_sliced(digest_partition *p, Csr which, const float *src0, int32_t ld0,
+                         const float *mask, int32_t ldm, const float *src1, int32_t ld1,
+                         int32_t d, float *out, int32_t ldo, bool relu, int32_t layer,
+                         hipStream_t s)
+{
+    const bool fwd = which == Csr::InH;
+    float *sl = p->at<float>(p->lay.slices);
+    Timed t(p, fwd ? K_SPMM_FWD : K_SPMM_BWD, layer, s);
+    if (digest_status st = hip_check(
+            digest::launch_slice_rows(p->n_own, d, src0, ld0, mask, ldm, sl, s), "slice rows"))
+        return st;
+    const auto &l = p->lay;
+    return hip_check(
+        digest::launch_spmm_slice(
+            p->at<SpmmBlock>(fwd ? l.blocks_s_slice : l.blocks_t_slice),
+            (int32_t)(fwd ? p->blocks_s_slice : p->blocks_t_slice).size(),
+            fwd ? p->long_s_slice : p->long_t_slice,
+            p->at<int32_t>(fwd ? l.s_rowptr : l.t_rowptr),
+            p->at<int32_t>(fwd ? l.s_col : l.t_src), p->at<float>(fwd ? l.s_val : l.t_val), sl,
+            p->n_own, src1, ld1, d, out, ldo, relu, s),
+        "sliced spmm");
 }
 
 digest_status run_spmm(digest_partition *p, Csr which, const float *src0, const float *src1,
@@ -942,6 +1052,10 @@ digest_status run_spmm(digest_partition *p, Csr which, const float *src0, const 
                        const digest::SpmmRank1 *r1 = nullptr, int32_t lds = 0,
                        int32_t out_ld = 0, int32_t out_w = 0)
 {
+    if (which == Csr::InT && !ep && !val && !relu && !out1 && !(r1 && r1->a) && kind < 0 &&
+        !find_tiers(*p, which, d) && sliced_pays(*p, d))
+        return run_sliced(p, which, src0, lds > 0 ? lds : d, nullptr, 0, nullptr, 0,
+                          out_w > 0 ? out_w : d, out, out_ld > 0 ? out_ld : d, false, layer, s);
     const bool fwd = which == Csr::Fwd;
     const std::vector<SpmmBlock> *blocks = &p->blocks_f;
     size_t boff = p->lay.blocks_f;
@@ -999,6 +1113,13 @@ digest_status run_spmm(digest_partition *p, Csr which, const float *src0, const 
                             n_src0, d, out, s, ep, out1, n_out0, relu, r1, false, lds, out_ld,
                             out_w),
         "spmm");
+}
+
+// An aggregate-first forward whose aggregation runs out of the L2s.
+bool use_sliced(const digest_partition &p, int32_t layer)
+{
+    return sliced_pays(p, p.widths[layer - 1]) && !fuse_forward(p, layer, false) &&
+           !find_tiers(p, Csr::InH, padded_width(p.widths[layer - 1]));
 }
 
 // S = P_b halo_buf[level]: the halo aggregate of level `level` (the halo
@@ -1247,6 +1368,14 @@ digest_status digest_partition_create(int64_t n_global, const int64_t *indptr,
                                                  p->t_rowptr.end());
             p->long_th = build_blocks(halo_rows, p->n_halo, p->blocks_th);
         }
+        for (int32_t k = 0; k <= p->L; ++k)
+            if (sliced_pays(*p, p->widths[k])) {
+                p->long_s_slice =
+                    build_slice_blocks(p->s_rowptr.data(), p->n_own, p->blocks_s_slice);
+                p->long_t_slice =
+                    build_slice_blocks(p->t_rowptr.data(), p->n_own, p->blocks_t_slice);
+                break;
+            }
         plan_tiers(*p);
         plan_layout(*p);
         plan_gat_layout(*p);
@@ -1348,6 +1477,10 @@ digest_status digest_partition_bind_workspace(digest_partition *p, void *dev_ptr
         {l.blocks_s_rows, p->blocks_s_rows.data(), sizeof(SpmmBlock) * p->blocks_s_rows.size()},
         {l.blocks_t_rows, p->blocks_t_rows.data(), sizeof(SpmmBlock) * p->blocks_t_rows.size()},
         {l.blocks_b, p->blocks_b.data(), sizeof(SpmmBlock) * p->blocks_b.size()},
+        {l.blocks_s_slice, p->blocks_s_slice.data(),
+         sizeof(SpmmBlock) * p->blocks_s_slice.size()},
+        {l.blocks_t_slice, p->blocks_t_slice.data(),
+         sizeof(SpmmBlock) * p->blocks_t_slice.size()},
     };
     for (const Up &u : ups) {
         if (!u.bytes)
@@ -1539,7 +1672,12 @@ digest_status digest_layer_forward(digest_partition *p, int32_t layer, const flo
             if (digest_status st = transform_rows(p, layer, h_in, hs, p->n_bnd, w, T, ldt, s))
                 return st;
         }
-        if (digest_status st = run_spmm(p, Csr::InH, T, nullptr, p->n_own + p->n_bnd, ldt,
+        if (sliced_pays(*p, d_out)) {
+            if (digest_status st = run_sliced(p, Csr::InH, T, ldt, nullptr, 0,
+                                              T + (int64_t)p->n_own * ldt, ldt, d_out, h_out,
+                                              d_out, act == DIGEST_ACT_RELU, layer, s))
+                return st;
+        } else if (digest_status st = run_spmm(p, Csr::InH, T, nullptr, p->n_own + p->n_bnd, ldt,
                                         h_out, layer, s, nullptr, -1, nullptr, INT32_MAX,
                                         nullptr, act == DIGEST_ACT_RELU, nullptr, ldt, d_out,
                                         d_out))
@@ -1552,7 +1690,8 @@ digest_status digest_layer_forward(digest_partition *p, int32_t layer, const flo
         float *ah = p->at<float>(p->lay.ah[layer]);
         const int32_t lh = padded_width(d_in);
         const float *src0 = h_in;
-        if (lh != d_in) {
+        const bool sliced = use_sliced(*p, layer);
+        if (lh != d_in && !sliced) {
             float *hp = p->at<float>(p->lay.hpad);
             Timed t(p, K_PAD_ROWS, layer, s);
             if (digest_status st = hip_check(digest::launch_copy_rows(nullptr, nullptr, p->n_own,
@@ -1591,8 +1730,14 @@ digest_status digest_layer_forward(digest_partition *p, int32_t layer, const flo
             p->fwd_gen[layer] = p->pull_gen[layer - 1];
             return DIGEST_OK;
         }
-        if (digest_status st = run_spmm(p, Csr::InH, src0, hs, p->n_own, lh, ah, layer, s))
+        if (sliced) {
+            if (digest_status st = run_sliced(p, Csr::InH, h_in, d_in, nullptr, 0, hs, lh, d_in,
+                                              ah, lh, false, layer, s))
+                return st;
+        } else if (digest_status st =
+                       run_spmm(p, Csr::InH, src0, hs, p->n_own, lh, ah, layer, s)) {
             return st;
+        }
         Timed t(p, K_GEMM_FWD, layer, s);
         if (narrow_out(d_in, d_out)) {
             if (digest_status st = hip_check(
@@ -1753,7 +1898,15 @@ digest_status backward_transform_first(digest_partition *p, int32_t layer, const
     // whole float4 vectors wide; G keeps the padding columns (never read).
     const float *src = dh_out;
     int32_t dg = d_out, lsrc = d_out;   // gathered width, row stride of src
-    if (p->act[layer] == DIGEST_ACT_RELU) {
+    const bool relu = p->act[layer] == DIGEST_ACT_RELU;
+    // An aggregation out of the L2s masks D and pads its rows while laying
+    // it out; only the halo rows' aggregation still reads rows of D.
+    const bool sliced = !fused_dh && !dh_halo && sliced_pays(*p, d_out);
+    if (sliced) {
+        if (digest_status st = run_sliced(p, Csr::InT, dh_out, d_out, relu ? h_out : nullptr,
+                                          d_out, nullptr, 0, d_out, G, ldg, false, layer, s))
+            return st;
+    } else if (relu) {
         float *dm = p->at<float>(p->lay.hpad);
         Timed t(p, K_RELU_MASK, layer, s);
         if (digest_status st = hip_check(digest::launch_relu_mask(p->n_own, d_out, dh_out, d_out,
@@ -1774,10 +1927,11 @@ digest_status backward_transform_first(digest_partition *p, int32_t layer, const
         src = dp;
         dg = lsrc = ldg;
     }
-    if (digest_status st = run_spmm(p, Csr::InT, src, nullptr, p->n_own, dg, G, layer, s,
-                                    fused_dh ? &ep : nullptr, -1, nullptr, INT32_MAX, nullptr,
-                                    false, nullptr, lsrc, ldg, dg))
-        return st;
+    if (!sliced)
+        if (digest_status st = run_spmm(p, Csr::InT, src, nullptr, p->n_own, dg, G, layer, s,
+                                        fused_dh ? &ep : nullptr, -1, nullptr, INT32_MAX,
+                                        nullptr, false, nullptr, lsrc, ldg, dg))
+            return st;
     if (dh_halo) {
         // G_halo = P_out^T D; dh_halo = G_halo W^T (in the same launch when
         // the epilogue applies)
@@ -1793,9 +1947,12 @@ digest_status backward_transform_first(digest_partition *p, int32_t layer, const
     }
     if (p->n_bnd > 0) {
         Timed t(p, K_BND_ROWS, layer, s);
+        const int32_t *bnd = p->at<int32_t>(p->lay.bnd_local);
         if (digest_status st = hip_check(
-                digest::launch_copy_rows(p->at<int32_t>(p->lay.bnd_local), nullptr, p->n_bnd, dg,
-                                         src, G2, s, lsrc, ldg),
+                sliced && relu
+                    ? digest::launch_relu_mask(p->n_bnd, d_out, dh_out, d_out, h_out, d_out, G2,
+                                               ldg, s, bnd)
+                    : digest::launch_copy_rows(bnd, nullptr, p->n_bnd, dg, src, G2, s, lsrc, ldg),
                 "boundary rows"))
             return st;
     }
@@ -2609,9 +2766,14 @@ digest_status digest_profile_model(const digest_partition *p, int32_t model, dou
                 4 * (n + 1) + 8 * nnz_in + 8 * n * dout +
                     (pl.dgrad_fused ? 4 * (n * di + di * dout) : 0.0),
                 0.0, p->nnz_in);
+            // (a sliced aggregation masks and pads D itself; a ReLU layer's
+            // boundary rows are then masked as they are copied)
+            const bool sliced = !pl.dgrad_fused && sliced_pays(*p, p->widths[l]);
             if (p->n_bnd > 0)
-                put(K_BND_ROWS, l, 8 * nb * dout + 4 * nb);
-            if (relu)   // D formed once
+                put(K_BND_ROWS, l, (sliced && relu ? 12 : 8) * nb * dout + 4 * nb);
+            if (sliced)
+                ;
+            else if (relu)   // D formed once
                 put(K_RELU_MASK, l, 12 * n * dout);
             else if (!pl.dgrad_fused && p->widths[l] % 4)   // the padded copy of dh_out
                 put(K_PAD_ROWS, l, 4 * n * (dout + padded_width(p->widths[l])));
@@ -2638,7 +2800,7 @@ digest_status digest_profile_model(const digest_partition *p, int32_t model, dou
                 p->nnz_s);
             put(K_GEMM_FWD, l, 4 * (n * di + di * dout + n * dout), 2 * n * di * dout);
         }
-        if (p->widths[l - 1] % 4)   // the padded copy of h_in
+        if (p->widths[l - 1] % 4 && !use_sliced(*p, l))   // the padded copy of h_in
             put(K_PAD_ROWS, l, 4 * n * (di + padded_width(p->widths[l - 1])));
         put(K_GEMM_DW, l, 4 * (n * di + n * dout * (relu && !pl.backward_fused ? 2 : 1) + di * dout),
             2 * n * di * dout);

@@ -30,6 +30,8 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "kernels.h"
@@ -753,6 +755,288 @@ __global__ __launch_bounds__(256) void k_spmm_tier(
 }
 
 // ---------------------------------------------------------------------------
+// Sparse aggregation out of an XCD's L2
+// ---------------------------------------------------------------------------
+
+template <class F, int... U>
+__device__ __forceinline__ void unroll_seq(const F &f, std::integer_sequence<int, U...>)
+{
+    (f(std::integral_constant<int, U>{}), ...);
+}
+
+// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>).
+template <int N, class F>
+__device__ __forceinline__ void unroll(const F &f)
+{
+    unroll_seq(f, std::make_integer_sequence<int, N>{});
+}
+
+// v of lane U of the caller's group of 8 lanes: lane U of every row of 16
+// (row_newbcast), then lane 8 + U for the rows' upper halves.
+template <int U>
+__device__ __forceinline__ int group8_bcast(int v)
+{
+    static_assert(U >= 0 && U < 8, "a lane of the group");
+    const int lo = __builtin_amdgcn_update_dpp(0, v, 0x150 + U, 0xF, 0xF, false);
+    return __builtin_amdgcn_update_dpp(lo, v, 0x150 + 8 + U, 0xF, 0xC, false);
+}
+
+// The entries of one row block by block, over one column slice of kSliceFloats
+// floats (base: the slice's rows, kSliceFloats apart).  Eight lanes take an
+// entry, so a load instruction gathers eight entries' 128-byte slices.  Entry
+// ids and weights come 64 at a time, coalesced; a shuffle hands lane l of
+// group g the entry 8 l + g, so that step u takes the entries 8 u .. 8 u + 7
+// and a short last block skips whole steps.  (Fetched in that order instead,
+// each index load touches as many cache lines as a gather.)
+struct SliceBlock {
+    static constexpr int GL = kSliceFloats / 4, G = kWave / GL;
+    int off;   // byte offset of this lane's entry's row
+    float a;   // its weight
+
+    // entries k0 .. k0 + 63 below ke; a lane past them reads the row's last
+    // entry (an empty row: entry 0) with weight 0
+    __device__ __forceinline__ void fetch(const int32_t *__restrict__ col,
+                                          const float *__restrict__ val, int32_t k0, int32_t ke)
+    {
+        const int32_t k = k0 + (int32_t)(threadIdx.x & (kWave - 1));
+        const int32_t kc = k < ke ? k : (k0 < ke ? ke - 1 : 0);
+        off = col[kc] * (kSliceFloats * 4);
+        a = k < ke ? val[kc] : 0.f;
+    }
+    // acc += the block's nb entries, summed by themselves first (a chain of at
+    // most eight terms, then one per block, keeps the rounding of a long row
+    // below that of the 32 partial sums the whole-row kernel splits it into)
+    __device__ __forceinline__ void add(const float *__restrict__ base, int nb, float (&acc)[4])
+    {
+        const int lane = threadIdx.x & (kWave - 1);
+        const int gl = lane % GL, mine = gl * G + lane / GL;
+        const int o = __shfl(off, mine);
+        const int w = __float_as_int(__shfl(a, mine));
+        float4 x[GL];
+        float sum[4] = {0.f, 0.f, 0.f, 0.f};
+        auto load = [&](auto uc) {
+            constexpr int u = decltype(uc)::value;
+            const uint32_t at = (uint32_t)group8_bcast<u>(o) + (uint32_t)(gl * 16);
+            x[u] = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(base) + at);
+        };
+        auto fma4 = [&](auto uc) {
+            constexpr int u = decltype(uc)::value;
+            const float wu = __int_as_float(group8_bcast<u>(w));
+            sum[0] = fmaf(wu, x[u].x, sum[0]);
+            sum[1] = fmaf(wu, x[u].y, sum[1]);
+            sum[2] = fmaf(wu, x[u].z, sum[2]);
+            sum[3] = fmaf(wu, x[u].w, sum[3]);
+        };
+        if (nb > kWave - G) {   // every step has entries
+            unroll<GL>(load);
+            unroll<GL>(fma4);
+        } else {   // uniform branches: the steps that have entries
+            unroll<GL>([&](auto uc) {
+                if (decltype(uc)::value * G < nb)
+                    load(uc);
+            });
+            unroll<GL>([&](auto uc) {
+                if (decltype(uc)::value * G < nb)
+                    fma4(uc);
+            });
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            acc[v] += sum[v];
+    }
+};
+
+// Sums a wave's groups of 8 lanes, each lane holding four features:
+// afterwards lane l of 16-lane row q holds the total of feature
+// 4 (l % 8) + {0, 2, 1, 3}[q] of the slice.  Halves, then rows, are summed
+// while two components change places (three exchanges for four features),
+// then the two groups inside a row.
+__device__ __forceinline__ float slice_reduce(const float (&x)[4])
+{
+    auto swap32 = [](float a, float b) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b),
+                                                        false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    };
+    const float s01 = swap32(x[0], x[1]), s23 = swap32(x[2], x[3]);
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(s01), __float_as_uint(s23),
+                                                    false, false);
+    const float s = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    return s + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x128, 0xF, 0xF,
+                                                          false));   // row_ror:8
+}
+
+// Aggregation out[r] = sum_k val[k] src[col[k]] over a source laid out in
+// column slices of kSliceFloats floats ([slice][row][32], launch_slice_rows),
+// each slice gathered by one XCD so that it stays in that XCD's L2: logical
+// workgroup (slice, w) with the slices dealt to the XCDs in contiguous runs.
+// The blocks are strips of consecutive rows for one wave (nrows > 0), by
+// descending entry count, kSpmmWaves to a workgroup; before them come n_long
+// rows whose entries a whole workgroup splits.  A wave requests the next
+// entries (of the row, or of the strip's next row) before the gathers of
+// the current ones.  With TWO a row's last entry may name a column c >=
+// n_src0 (with weight 1): row c - n_src0 of src1, read as it is (row stride
+// ld1) where the row's sum is stored.  The first d columns of a row are
+// stored, relu stores max(x, 0).
+// Bound by the L2s' random 128-byte reads: the Reddit-shaped partition
+// (29,125 rows, 10.4 M entries, 256 floats) gathers 10.6 GB in 535 us, the
+// layout pass (about 15) included: 20 TB/s, where a bare random gather of
+// such lines reaches 24.  The row-per-wave kernel took 1,161 us: its gathers
+// miss the L2 and are bound by the fabric's 8-9 TB/s.  Three choices matter:
+// plain index loads (nontemporal ones: 690 us), the sums' exchange by
+// permlane swaps, twelve shuffles before, with the next row's entries
+// requested ahead (5 M entries over 24,000 rows: 301 to 246 us), and the
+// slices laid out one after another (read in place, rows 1 KB apart use an
+// eighth of the L2's sets: 660 us).
+template <bool TWO>
+__global__ __launch_bounds__(kSpmmThreads, 8) void k_spmm_slice(
+    const SpmmBlock *__restrict__ blocks, int32_t n_long, int32_t n_blocks, uint32_t per_slice,
+    const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
+    const float *__restrict__ val, const float *__restrict__ src, int64_t slice_stride,
+    int32_t n_src0, const float *__restrict__ src1, int32_t ld1, int32_t d,
+    float *__restrict__ out, int32_t ldo, bool relu)
+{
+    constexpr int SW = kSliceFloats;
+    __shared__ float red[kSpmmWaves][SW];
+    const uint32_t logical = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int32_t slice = (int32_t)(logical / per_slice);
+    const int32_t w = (int32_t)(logical % per_slice);
+    const float *base = src + slice * slice_stride;
+    const int32_t off = slice * SW;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int lane = threadIdx.x & (kWave - 1);
+    // the feature this lane holds after slice_reduce
+    const int q = lane / 16;
+    const int f = 4 * (lane % 8) + (q == 1 ? 2 : q == 2 ? 1 : q);
+    const bool holds = lane % 16 < 8;
+    // row [kb, ke)'s second source: -1 or its row of src1, ke without it
+    auto second = [&](int32_t kb, int32_t &ke) -> int32_t {
+        if (!TWO || ke <= kb)
+            return -1;
+        const int32_t c = col[ke - 1] - n_src0;   // uniform
+        if (c < 0)
+            return -1;
+        --ke;
+        return c;
+    };
+    SliceBlock cur, next;
+    if (w < n_long) {   // uniform over the workgroup
+        const SpmmBlock b = blocks[w];
+        int32_t bke = b.ke;
+        const int32_t sec = second(b.kb, bke);
+        const int32_t per = (bke - b.kb + kSpmmWaves - 1) / kSpmmWaves;
+        const int32_t kb = min(bke, b.kb + wave * per);
+        const int32_t ke = min(bke, kb + per);
+        float acc[4] = {0.f, 0.f, 0.f, 0.f};
+        cur.fetch(col, val, kb, ke);
+        for (int32_t k0 = kb; k0 < ke; k0 += kWave) {
+            if (k0 + kWave < ke)
+                next.fetch(col, val, k0 + kWave, ke);
+            cur.add(base, ke - k0, acc);
+            cur = next;
+        }
+        const float s = slice_reduce(acc);
+        if (holds)
+            red[wave][f] = s;
+        __syncthreads();
+        const int t = threadIdx.x;
+        if (t < SW && off + t < d) {
+            float sum = sec >= 0 ? src1[(int64_t)sec * ld1 + off + t] : 0.f;
+#pragma unroll
+            for (int i = 0; i < kSpmmWaves; ++i)
+                sum += red[i][t];
+            out[(int64_t)b.row * ldo + off + t] = relu ? fmaxf(sum, 0.f) : sum;
+        }
+        return;
+    }
+    const int32_t bi = n_long + (w - n_long) * kSpmmWaves + wave;
+    if (bi >= n_blocks)
+        return;
+    const SpmmBlock b = blocks[bi];
+    const int32_t rend = b.row + b.nrows;
+    int32_t r = b.row;
+    int32_t k0 = rowptr[r], kend = rowptr[r + 1];   // the next row begins at kend
+    int32_t ke = kend;
+    int32_t sec = second(k0, ke);
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    cur.fetch(col, val, k0, ke);
+    while (true) {
+        const bool last = k0 + kWave >= ke;   // the row's last block (uniform)
+        if (!last) {
+            next.fetch(col, val, k0 + kWave, ke);
+            cur.add(base, ke - k0, acc);
+            cur = next;
+            k0 += kWave;
+            continue;
+        }
+        // the strip's next row (past the strip: an empty one, reading entry 0)
+        const int32_t nk0 = kend;
+        kend = rowptr[min(r + 2, rend)];
+        int32_t nke = kend;
+        const int32_t nsec = second(nk0, nke);
+        next.fetch(col, val, nk0, nke);
+        float extra = 0.f;
+        if (TWO && sec >= 0 && holds && off + f < d)
+            extra = src1[(int64_t)sec * ld1 + off + f];
+        cur.add(base, ke - k0, acc);
+        const float s = slice_reduce(acc) + extra;
+        if (holds && off + f < d)
+            out[(int64_t)r * ldo + off + f] = relu ? fmaxf(s, 0.f) : s;
+        if (++r >= rend)
+            return;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            acc[v] = 0.f;
+        cur = next;
+        k0 = nk0;
+        ke = nke;
+        sec = nsec;
+    }
+}
+
+// dst[slice][r][32] = the rows of src (row stride lds), d floats wide, in
+// column slices of kSliceFloats floats; columns past d are zero.  With MASK
+// an element is zeroed unless h's (same shape, row stride ldh) is positive.
+// A thread moves four floats.
+template <bool VEC, bool MASK>
+__global__ __launch_bounds__(256) void k_slice_rows(int32_t n, int32_t d,
+                                                    const float *__restrict__ src, int32_t lds,
+                                                    const float *__restrict__ h, int32_t ldh,
+                                                    int32_t quads, float *__restrict__ dst)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= (int64_t)n * quads)
+        return;
+    const int32_t r = (int32_t)(i / quads);
+    const int32_t c = (int32_t)(i % quads) * 4;
+    const float *p = src + (int64_t)r * lds + c;
+    const float *m = MASK ? h + (int64_t)r * ldh + c : nullptr;
+    float x[4] = {0.f, 0.f, 0.f, 0.f}, y[4] = {1.f, 1.f, 1.f, 1.f};
+    if (VEC) {   // whole float4s up to d rounded up to 4
+        if (c < d) {
+            load_vec<4>(p, x);
+            if (MASK)
+                load_vec<4>(m, y);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            x[v] = c + v < d && y[v] > 0.f ? x[v] : 0.f;
+    } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            if (c + v < d) {
+                x[v] = p[v];
+                if (MASK)
+                    x[v] = m[v] > 0.f ? x[v] : 0.f;
+            }
+        }
+    }
+    store_vec<4>(dst + (int64_t)(c / kSliceFloats) * n * kSliceFloats +
+                     (int64_t)r * kSliceFloats + c % kSliceFloats,
+                 x);
+}
+
+// ---------------------------------------------------------------------------
 // fp32 MFMA GEMM
 // ---------------------------------------------------------------------------
 
@@ -990,9 +1274,11 @@ __global__ __launch_bounds__(256) void k_gemm(int32_t M, int32_t N, int32_t K, i
 }
 
 // out[r][c] = h[r][c] > 0 ? g[r][c] : 0 for r < n, c < d (row strides ldg,
-// ldh, ldo), VEC floats per thread.
+// ldh, ldo), VEC floats per thread; with idx, row idx[r] of g and h.
 template <int VEC>
-__global__ __launch_bounds__(256) void k_relu_mask(int64_t n, int32_t d, const float *__restrict__ g,
+__global__ __launch_bounds__(256) void k_relu_mask(int64_t n, int32_t d,
+                                                   const int32_t *__restrict__ idx,
+                                                   const float *__restrict__ g,
                                                    int32_t ldg, const float *__restrict__ h,
                                                    int32_t ldh, float *__restrict__ out,
                                                    int32_t ldo)
@@ -1004,8 +1290,9 @@ __global__ __launch_bounds__(256) void k_relu_mask(int64_t n, int32_t d, const f
     const int64_t r = i / dv;
     const int32_t c = (int32_t)(i % dv) * VEC;
     float gv[VEC], hv[VEC];
-    load_vec<VEC>(g + r * ldg + c, gv);
-    load_vec<VEC>(h + r * ldh + c, hv);
+    const int64_t sr = idx ? idx[r] : r;
+    load_vec<VEC>(g + sr * ldg + c, gv);
+    load_vec<VEC>(h + sr * ldh + c, hv);
 #pragma unroll
     for (int v = 0; v < VEC; ++v)
         gv[v] = hv[v] > 0.f ? gv[v] : 0.f;
@@ -2414,6 +2701,62 @@ hipError_t launch_spmm_sliced(const SpmmBlock *blocks, int32_t n_blocks, int32_t
     return hipErrorInvalidValue;   // rows of odd width take the unsliced kernel
 }
 
+hipError_t launch_slice_rows(int32_t n, int32_t d, const float *src, int32_t lds, const float *h,
+                             int32_t ldh, float *dst, hipStream_t s)
+{
+    if (n <= 0 || d <= 0)
+        return hipSuccess;
+    if (lds < d || (h && ldh < d))
+        return hipErrorInvalidValue;
+    auto ok = [&](const float *p, int32_t ld) {
+        return ((uintptr_t)p % 16) == 0 && ld % 4 == 0;
+    };
+    const bool vec = ok(src, lds) && (!h || ok(h, ldh));
+    const int32_t quads = (d + kSliceFloats - 1) / kSliceFloats * (kSliceFloats / 4);
+    const int64_t grid = ((int64_t)n * quads + 255) / 256;
+    if (grid > 0x7fffffff)
+        return hipErrorInvalidConfiguration;
+#define DIGEST_SLICE(V, M)                                                                     \
+    hipLaunchKernelGGL((k_slice_rows<V, M>), dim3((unsigned)grid), dim3(256), 0, s, n, d, src,  \
+                       lds, h, ldh, quads, dst)
+    if (vec && h)
+        DIGEST_SLICE(true, true);
+    else if (vec)
+        DIGEST_SLICE(true, false);
+    else if (h)
+        DIGEST_SLICE(false, true);
+    else
+        DIGEST_SLICE(false, false);
+#undef DIGEST_SLICE
+    return hipGetLastError();
+}
+
+hipError_t launch_spmm_slice(const SpmmBlock *blocks, int32_t n_blocks, int32_t n_long,
+                             const int32_t *rowptr, const int32_t *col, const float *val,
+                             const float *src, int32_t n_src, const float *src1, int32_t ld1,
+                             int32_t d, float *out, int32_t ldo, bool relu, hipStream_t s)
+{
+    if (n_blocks <= 0 || d <= 0)
+        return hipSuccess;
+    if (n_long < 0 || n_long > n_blocks || ldo < d || n_src < 1 || (src1 && ld1 < d) ||
+        (int64_t)n_src * kSliceFloats * 4 > INT32_MAX)   // byte offsets within a slice
+        return hipErrorInvalidValue;
+    const int64_t per = n_long + ((int64_t)(n_blocks - n_long) + kSpmmWaves - 1) / kSpmmWaves;
+    const int64_t grid = per * ((d + kSliceFloats - 1) / kSliceFloats);
+    if (grid > 0x7fffffff)
+        return hipErrorInvalidConfiguration;
+    const int64_t stride = (int64_t)n_src * kSliceFloats;
+    if (src1)
+        hipLaunchKernelGGL(k_spmm_slice<true>, dim3((unsigned)grid), dim3(kSpmmThreads), 0, s,
+                           blocks, n_long, n_blocks, (uint32_t)per, rowptr, col, val, src, stride,
+                           n_src, src1, ld1, d, out, ldo, relu);
+    else
+        hipLaunchKernelGGL(k_spmm_slice<false>, dim3((unsigned)grid), dim3(kSpmmThreads), 0, s,
+                           blocks, n_long, n_blocks, (uint32_t)per, rowptr, col, val, src, stride,
+                           n_src, nullptr, 0, d, out, ldo, relu);
+    return hipGetLastError();
+}
+
 hipError_t launch_spmm(const SpmmBlock *blocks, int32_t n_blocks, int32_t n_long,
                        const int32_t *rowptr, const int32_t *col, const float *val,
                        const float *src0, const float *src1, int32_t n_src0, int32_t d,
@@ -2520,7 +2863,8 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
 }
 
 hipError_t launch_relu_mask(int64_t n, int32_t d, const float *g, int32_t ldg, const float *h,
-                            int32_t ldh, float *out, int32_t ldo, hipStream_t s)
+                            int32_t ldh, float *out, int32_t ldo, hipStream_t s,
+                            const int32_t *idx)
 {
     if (n <= 0 || d <= 0)
         return hipSuccess;
@@ -2532,11 +2876,11 @@ hipError_t launch_relu_mask(int64_t n, int32_t d, const float *g, int32_t ldg, c
     if (grid > 0x7fffffff)
         return hipErrorInvalidConfiguration;
     if (v4)
-        hipLaunchKernelGGL((k_relu_mask<4>), dim3((unsigned)grid), dim3(256), 0, s, n, d, g, ldg,
-                           h, ldh, out, ldo);
+        hipLaunchKernelGGL((k_relu_mask<4>), dim3((unsigned)grid), dim3(256), 0, s, n, d, idx, g,
+                           ldg, h, ldh, out, ldo);
     else
-        hipLaunchKernelGGL((k_relu_mask<1>), dim3((unsigned)grid), dim3(256), 0, s, n, d, g, ldg,
-                           h, ldh, out, ldo);
+        hipLaunchKernelGGL((k_relu_mask<1>), dim3((unsigned)grid), dim3(256), 0, s, n, d, idx, g,
+                           ldg, h, ldh, out, ldo);
     return hipGetLastError();
 }
 

@@ -95,6 +95,18 @@ hipError_t launch_spmm_sliced(const SpmmBlock *blocks, int32_t n_blocks, int32_t
                               int64_t nnz, const float *src0, const float *src1, int32_t n_src0,
                               int32_t n_rows, int32_t d, float *out0, bool acc, hipStream_t s);
 
+// Aggregation of the rows named by the blocks out of a source of n_src rows
+// laid out in column slices, [slice][n_src][kSliceFloats] (launch_slice_rows,
+// which also applies the ReLU mask h > 0 if h is given), so that the slice
+// an XCD gathers stays in its L2.  A row's last entry may read row c - n_src
+// of src1 (c >= n_src, weight 1).  Stores d columns, row stride ldo.
+hipError_t launch_slice_rows(int32_t n, int32_t d, const float *src, int32_t lds, const float *h,
+                             int32_t ldh, float *dst, hipStream_t s);
+hipError_t launch_spmm_slice(const SpmmBlock *blocks, int32_t n_blocks, int32_t n_long,
+                             const int32_t *rowptr, const int32_t *col, const float *val,
+                             const float *src, int32_t n_src, const float *src1, int32_t ld1,
+                             int32_t d, float *out, int32_t ldo, bool relu, hipStream_t s);
+
 // An aggregation and a product in one pass: AH = the aggregation of rows
 // 0 .. n_rows-1 (as launch_spmm, sources of row stride lds, d floats
 // gathered) is stored to ah (row stride ld_ah, columns d .. ld_ah zero; ah
@@ -120,9 +132,10 @@ hipError_t launch_spmm_gemm(int32_t n_rows, const int32_t *rowptr, const int32_t
                             int32_t N, float *C, int32_t ldc, bool relu, hipStream_t s);
 
 // out[r][c] = h[r][c] > 0 ? g[r][c] : 0 (the ReLU derivative applied), row
-// strides ldg, ldh, ldo.
+// strides ldg, ldh, ldo; with idx, g and h rows are idx[r].
 hipError_t launch_relu_mask(int64_t n, int32_t d, const float *g, int32_t ldg, const float *h,
-                            int32_t ldh, float *out, int32_t ldo, hipStream_t s);
+                            int32_t ldh, float *out, int32_t ldo, hipStream_t s,
+                            const int32_t *idx = nullptr);
 // dst (cols x rows) = src^T for a row-major rows x cols src.
 hipError_t launch_transpose(int32_t rows, int32_t cols, const float *src, float *dst,
                             hipStream_t s);
