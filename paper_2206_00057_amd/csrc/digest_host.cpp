@@ -137,14 +137,15 @@ void splitk_plan(int64_t M, int64_t N, int64_t K, int32_t &splits, int32_t &kchu
 }
 
 // Workgroup tile of C for a GEMM (see GemmArgs::tile): 64x64 keeps enough
-// workgroups for the partition-sized products and for every split-K weight
-// gradient; tall products (>= 20,000 rows) run faster on 128x128 tiles,
-// whose waves each own a 64x64 block (one LDS fragment read per MFMA).
+// workgroups for the partition-sized products (11,250 x 256 over 500: 33 us,
+// 128x128 41) and for every split-K weight gradient; tall products run
+// faster on 128x128 tiles, which stage each operand half as often (two times
+// 29,125 x 256 over 602: 180 / 148 us).
 int32_t gemm_tile_for(int64_t M, int64_t N, int64_t K, bool contraction_over_rows)
 {
     if (contraction_over_rows)
         return 0;
-    return (M >= 20000 && N >= 128) ? 3 : 0;
+    return (M >= 20000 && N >= 128) ? 1 : 0;
 }
 
 // A CSR's first n_rows rows split at kFuseLong entries, for the fused
@@ -1159,7 +1160,7 @@ digest_status halo_aggregate(digest_partition *p, int32_t level, hipStream_t s,
 // GEMM for the owned and for the second block's rows.
 digest_status transform_rows(digest_partition *p, int32_t layer, const float *h_own,
                              const float *h2, int32_t n2, const float *w, float *T, int32_t ldt,
-                             hipStream_t s)
+                             hipStream_t s, bool f32 = false)
 {
     const int32_t d_in = p->widths[layer - 1], d_out = p->widths[layer];
     if (narrow_out(d_in, d_out))
@@ -1176,6 +1177,7 @@ digest_status transform_rows(digest_partition *p, int32_t layer, const float *h_
     g.ldc = ldt;
     g.splits = 1;
     g.kchunk = d_in;
+    g.f32 = f32;
     if (p->n_own > 0) {
         g.M = p->n_own;
         g.A = h_own;
@@ -2463,7 +2465,7 @@ digest_status digest_gat_forward(digest_partition *p, int32_t layer, const float
     {
         Timed t(p, K_GAT_TRANSFORM, layer, s);
         if (digest_status st = transform_rows(p, layer, h_in, halo, p->n_halo, w, Z,
-                                              p->widths[layer], s))
+                                              p->widths[layer], s, true))
             return st;
     }
     {

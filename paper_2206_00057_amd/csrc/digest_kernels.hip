@@ -12,9 +12,9 @@
 //                  64 at a time and broadcast, many gathers are kept in
 //                  flight, and groups are combined by a butterfly.  Results
 //                  are deterministic; no float atomics, no global fences.
-//   k_gemm         fp32 MFMA (v_mfma_f32_32x32x2f32) GEMM with optional
-//                  transposed operands, ReLU-derivative operand masks, a
-//                  ReLU epilogue and split-K; tiles are dealt to the XCDs in
+//   k_gemm         GEMM in fp32 precision on the bf16 matrix cores (operands
+//                  split into three bf16) with optional transposed operands,
+//                  ReLU-derivative operand masks, a ReLU epilogue and split-K; tiles are dealt to the XCDs in
 //                  contiguous runs (shared operand strips share an L2): the dense
 //                  transform AH W, the weight gradient AH^T D and D W^T.
 //   k_splitk_reduce  deterministic sum of split-K partial products.
@@ -1037,29 +1037,368 @@ __global__ __launch_bounds__(256) void k_slice_rows(int32_t n, int32_t d,
 }
 
 // ---------------------------------------------------------------------------
-// fp32 MFMA GEMM
+// fp32 GEMM on the bf16 matrix cores
 // ---------------------------------------------------------------------------
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+
+// A workgroup barrier for data in LDS alone: __syncthreads() also waits for
+// the global loads in flight, which are the next tiles.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Eight floats as the sums of three bf16 each, x = h + m + l: h is x rounded
+// to bf16, m what is left rounded, l what is left then (each step's
+// remainder is exact in fp32, and the three hold all 24 bits of x).
+__device__ __forceinline__ void split8(const float (&x)[8], uint4 &h, uint4 &m, uint4 &l)
+{
+    uint32_t hu[4], mu[4], lu[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float a = x[2 * i], b = x[2 * i + 1];
+        hu[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{a, b}), bf16x2));
+        a -= __uint_as_float(hu[i] << 16);
+        b -= __uint_as_float(hu[i] & 0xffff0000u);
+        mu[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{a, b}), bf16x2));
+        a -= __uint_as_float(mu[i] << 16);
+        b -= __uint_as_float(mu[i] & 0xffff0000u);
+        lu[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{a, b}), bf16x2));
+    }
+    h = make_uint4(hu[0], hu[1], hu[2], hu[3]);
+    m = make_uint4(mu[0], mu[1], mu[2], mu[3]);
+    l = make_uint4(lu[0], lu[1], lu[2], lu[3]);
+}
+
+// Eight consecutive k of one row (or column) r of an operand.  KC: the
+// operand's memory runs along k (element (r, k) at r ld + k), else along r
+// (k ld + r).
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
+
+template <bool KC, bool MASK>
+struct Oct {
+    float v[8], m[MASK ? 8 : 1];
+
+    // From a uniform tile offset (floats) and a per-lane byte offset, without
+    // checks.
+    __device__ __forceinline__ void load(const float *__restrict__ base,
+                                         const float *__restrict__ mbase, int64_t tile,
+                                         uint32_t off, int64_t ld)
+    {
+        // (the empty asm keeps the uniform part in scalar registers, so that a
+        // load takes it and the lane's offset as they are)
+        auto at = [&](const float *b, int64_t o) {
+            o *= 4;
+            asm("" : "+s"(o));
+            return reinterpret_cast<const char *>(b) + o + off;
+        };
+        if constexpr (KC) {
+            // 16-byte loads at any 4-byte alignment, which global loads take
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const floatx4u a = *reinterpret_cast<const floatx4u *>(at(base, tile + 4 * q));
+                v[4 * q] = a.x, v[4 * q + 1] = a.y, v[4 * q + 2] = a.z, v[4 * q + 3] = a.w;
+                if constexpr (MASK) {
+                    const floatx4u b = *reinterpret_cast<const floatx4u *>(at(mbase, tile + 4 * q));
+                    m[4 * q] = b.x, m[4 * q + 1] = b.y, m[4 * q + 2] = b.z, m[4 * q + 3] = b.w;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                v[j] = *reinterpret_cast<const float *>(at(base, tile + j * ld));
+                if constexpr (MASK)
+                    m[j] = *reinterpret_cast<const float *>(at(mbase, tile + j * ld));
+            }
+        }
+    }
+    // Element by element, zero from k_lim on (a K range's last, partial tile).
+    __device__ __forceinline__ void load_tail(const float *__restrict__ tile,
+                                              const float *__restrict__ mtile, uint32_t off,
+                                              int64_t ld, int k, int k_lim)
+    {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int64_t o = off / 4 + (KC ? j : j * ld);
+            const bool in = k + j < k_lim;
+            v[j] = in ? tile[o] : 0.f;
+            if constexpr (MASK)
+                m[j] = in ? mtile[o] : 0.f;
+        }
+    }
+    __device__ __forceinline__ void take(float (&x)[8]) const
+    {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            x[j] = v[j];
+            if constexpr (MASK)
+                x[j] = m[j] > 0.f ? x[j] : 0.f;
+        }
+    }
+};
+
+// C = op(A) op(B) in fp32 precision on v_mfma_f32_32x32x16_bf16: every
+// operand element is split into three bf16 (split8) as it is staged in LDS,
+// and of the nine products of the parts the six that reach fp32's last bits
+// are accumulated in fp32 (what is left out is below 2^-26 of a product):
+// the products of the high parts in one accumulator, the small ones in
+// another, added at the end, so that a sum is rounded once per 16 k (the
+// errors against 64 bits are about a third of the fp32 instructions': 500
+// deep 1.3e-7 against 4.1e-7, 3,200 deep 7e-7 against 1.7e-6).  A B_ x B_
+// tile of C per workgroup (64 or 128), 4 waves in 2x2, each TM x TN blocks of
+// 32x32; K advances 32 at a time, DEPTH tiles ahead in registers while one
+// is multiplied out of LDS ([row][k] per part, rows 80 bytes apart so that
+// sixteen lanes' 16-byte reads fall into different banks).
+// Rows past the operand repeat its last row (their results are not stored).
+// Six bf16 products cost 192 matrix-core cycles where the fp32 instructions
+// need 512 for the same 16 k; splitting costs 5.5 vector operations per
+// staged element, so addresses are a uniform tile base and a fixed offset
+// per lane, and nothing but the last tile of a K range is checked.
+// Measured (fp32 instructions / this): 11,250 x 256 over 500 44 / 33 us,
+// 58,250 x 256 over 602 247 / 148, weight gradients 500 x 256 over 11,250
+// 45 / 36, 602 x 256 over 58,250 243 / 171.  What is left is the chain of
+// phases between the barriers: a second LDS buffer with one barrier per tile
+// cost occupancy and was slower (38 and 210 us), and so were three and four
+// tiles in flight.
+// A non-finite operand (or one that rounds past bf16's largest value) makes
+// the split's parts NaN; an element of C that comes out non-finite is
+// therefore summed again in fp32 from memory.
+template <int B_, int DEPTH, bool AT, bool BT, bool AMASK, bool BMASK, bool RELU>
+__global__ __launch_bounds__(256, B_ > 64 ? 2 : 3) void k_gemm(
+    int32_t M, int32_t N, int32_t K, int32_t kchunk, const float *__restrict__ A, int32_t lda,
+    const float *__restrict__ Am, const float *__restrict__ B, int32_t ldb,
+    const float *__restrict__ Bm, float *__restrict__ C, int32_t ldc, int64_t c_split_stride,
+    int32_t gm, int32_t gn)
+{
+    constexpr int BK = kGemmBK, BM = B_, BN = B_;
+    constexpr int TM = BM / 64, TN = BN / 64;
+    constexpr int UA = BM * 4 / 256, UB = BN * 4 / 256;   // octs per thread
+    constexpr int LD = BK + 8;                            // bf16 between LDS rows
+    static_assert(BK == 32 && UA >= 1 && UB >= 1 && DEPTH >= 1, "tile");
+    __shared__ __attribute__((aligned(16))) uint16_t As[3][BM][LD];
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[3][BN][LD];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1);
+    const int wid = tid / kWave;
+    // logical tiles: split-major, then M strip, then N tile, so that an XCD
+    // holds whole K slices and the N tiles of an M strip (shared operands)
+    const uint32_t logical = xcd_contiguous(blockIdx.x, gridDim.x);
+    const uint32_t per_split = (uint32_t)gm * (uint32_t)gn;
+    const int z = (int)(logical / per_split);
+    const uint32_t t = logical % per_split;
+    const int m0 = (int)(t / (uint32_t)gn) * BM;
+    const int n0 = (int)(t % (uint32_t)gn) * BN;
+    const int kb = z * kchunk;
+    const int ke = min(K, kb + kchunk);
+    const int wm = (wid >> 1) * (BM / 2);
+    const int wn = (wid & 1) * (BN / 2);
+
+    floatx16 acc[TM][TN], low[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                acc[i][j][e] = low[i][j][e] = 0.f;
+
+    // oct u of an operand tile of R rows: k-contiguous operands take the
+    // four octs of a row side by side, others the rows side by side
+    struct Tile {
+        Oct<!AT, AMASK> a[UA];
+        Oct<BT, BMASK> b[UB];
+    };
+    auto row_of = [](bool kc, int u, int R) { return kc ? u / 4 : u % R; };
+    auto oct_of = [](bool kc, int u, int R) { return kc ? u % 4 : u / R; };
+    uint32_t offa[UA], offb[UB];
+#pragma unroll
+    for (int i = 0; i < UA; ++i) {
+        const int u = tid + 256 * i;
+        const uint32_t r = min(row_of(!AT, u, BM), M - 1 - m0), k = 8 * oct_of(!AT, u, BM);
+        offa[i] = 4u * (AT ? k * (uint32_t)lda + r : r * (uint32_t)lda + k);
+    }
+#pragma unroll
+    for (int i = 0; i < UB; ++i) {
+        const int u = tid + 256 * i;
+        const uint32_t r = min(row_of(BT, u, BN), N - 1 - n0), k = 8 * oct_of(BT, u, BN);
+        offb[i] = 4u * (BT ? r * (uint32_t)ldb + k : k * (uint32_t)ldb + r);
+    }
+    // The tiles in the order they are multiplied: the K range's partial tile
+    // (if any), checked, then the whole ones, unchecked.
+    const int tail = (ke - kb) % BK != 0, tiles = (ke - kb) / BK + tail;
+    auto fetch = [&](int i, Tile &x) {   // whole tile i (uniform)
+        const int k0 = kb + BK * (i - tail);
+        const int64_t ta = AT ? (int64_t)k0 * lda + m0 : (int64_t)m0 * lda + k0;
+        const int64_t tb = BT ? (int64_t)n0 * ldb + k0 : (int64_t)k0 * ldb + n0;
+#pragma unroll
+        for (int u = 0; u < UA; ++u)
+            x.a[u].load(A, Am, ta, offa[u], lda);
+#pragma unroll
+        for (int u = 0; u < UB; ++u)
+            x.b[u].load(B, Bm, tb, offb[u], ldb);
+    };
+    auto fetch_tail = [&](Tile &x) {
+        const int k0 = ke - (ke - kb) % BK;
+        const int64_t ta = AT ? (int64_t)k0 * lda + m0 : (int64_t)m0 * lda + k0;
+        const int64_t tb = BT ? (int64_t)n0 * ldb + k0 : (int64_t)k0 * ldb + n0;
+#pragma unroll
+        for (int u = 0; u < UA; ++u)
+            x.a[u].load_tail(A + ta, Am + ta, offa[u], lda,
+                             k0 + 8 * oct_of(!AT, tid + 256 * u, BM), ke);
+#pragma unroll
+        for (int u = 0; u < UB; ++u)
+            x.b[u].load_tail(B + tb, Bm + tb, offb[u], ldb,
+                             k0 + 8 * oct_of(BT, tid + 256 * u, BN), ke);
+    };
+    auto stash = [&](const Tile &y) {
+        float x[8];
+        uint4 h, m, l;
+#pragma unroll
+        for (int i = 0; i < UA; ++i) {
+            const int u = tid + 256 * i;
+            const int r = row_of(!AT, u, BM), k = 8 * oct_of(!AT, u, BM);
+            y.a[i].take(x);
+            split8(x, h, m, l);
+            *reinterpret_cast<uint4 *>(&As[0][r][k]) = h;
+            *reinterpret_cast<uint4 *>(&As[1][r][k]) = m;
+            *reinterpret_cast<uint4 *>(&As[2][r][k]) = l;
+        }
+#pragma unroll
+        for (int i = 0; i < UB; ++i) {
+            const int u = tid + 256 * i;
+            const int r = row_of(BT, u, BN), k = 8 * oct_of(BT, u, BN);
+            y.b[i].take(x);
+            split8(x, h, m, l);
+            *reinterpret_cast<uint4 *>(&Bs[0][r][k]) = h;
+            *reinterpret_cast<uint4 *>(&Bs[1][r][k]) = m;
+            *reinterpret_cast<uint4 *>(&Bs[2][r][k]) = l;
+        }
+    };
+    auto compute = [&]() {
+#pragma unroll
+        for (int s = 0; s < BK / 16; ++s) {
+            bf16x8 fa[3][TM], fb[3][TN];
+            const int k = 16 * s + 8 * (lane >> 5);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+                    fa[p][i] = *reinterpret_cast<const bf16x8 *>(
+                        &As[p][wm + 32 * i + (lane & 31)][k]);
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    fb[p][j] = *reinterpret_cast<const bf16x8 *>(
+                        &Bs[p][wn + 32 * j + (lane & 31)][k]);
+            }
+            constexpr int PA[6] = {0, 0, 1, 0, 1, 2}, PB[6] = {0, 1, 0, 2, 1, 0};
+#pragma unroll
+            for (int c = 0; c < 6; ++c)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        floatx16 &d = c == 0 ? acc[i][j] : low[i][j];
+                        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[PA[c]][i], fb[PB[c]][j],
+                                                                    d, 0, 0, 0);
+                    }
+        }
+    };
+    // Multiplies the tile held in x and requests tile i into it (the last
+    // one again past the end: an unconditional request, so that the waits
+    // count loads and leave the newer ones in flight).
+    auto step = [&](int i, Tile &x) {
+        stash(x);
+        lds_barrier();
+        fetch(min(i, tiles - 1), x);
+        compute();
+        lds_barrier();
+    };
+    Tile held[DEPTH];
+    if (tail)
+        fetch_tail(held[0]);
+    if (tiles == tail) {   // no whole tile
+        if (tail) {
+            stash(held[0]);
+            lds_barrier();
+            compute();
+        }
+    } else {
+        if (!tail)
+            fetch(0, held[0]);
+#pragma unroll
+        for (int d = 1; d < DEPTH; ++d)
+            fetch(min(d, tiles - 1), held[d]);
+        int i = 0;
+        for (; i + DEPTH <= tiles; i += DEPTH) {
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d)
+                step(i + d + DEPTH, held[d]);
+        }
+#pragma unroll
+        for (int d = 0; d + 1 < DEPTH; ++d)
+            if (i + d < tiles)   // uniform
+                step(tiles, held[d]);
+    }
+
+    float *Cz = C + (int64_t)z * c_split_stride;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int cn = n0 + wn + 32 * j + (lane & 31);
+            const int r0 = m0 + wm + 32 * i + (lane >> 5) * 4;
+            uint32_t bad = 0;   // bit e: element e is stored and not finite
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int r = r0 + (e >> 2) * 8 + (e & 3);
+                float v = acc[i][j][e] + low[i][j][e];
+                if (r < M && cn < N) {
+                    bad |= (__float_as_uint(v) & 0x7f800000u) == 0x7f800000u ? 1u << e : 0u;
+                    if (RELU)
+                        v = fmaxf(v, 0.f);
+                    Cz[(int64_t)r * ldc + cn] = v;
+                }
+            }
+            while (bad) {
+                const int e = __builtin_ctz(bad);
+                bad &= bad - 1;
+                const int r = r0 + (e >> 2) * 8 + (e & 3);
+                float v = 0.f;
+                for (int k = kb; k < ke; ++k) {
+                    const int64_t ia = AT ? (int64_t)k * lda + r : (int64_t)r * lda + k;
+                    const int64_t ib = BT ? (int64_t)cn * ldb + k : (int64_t)k * ldb + cn;
+                    const float a = AMASK && !(Am[ia] > 0.f) ? 0.f : A[ia];
+                    const float b = BMASK && !(Bm[ib] > 0.f) ? 0.f : B[ib];
+                    v = fmaf(a, b, v);
+                }
+                Cz[(int64_t)r * ldc + cn] = RELU ? fmaxf(v, 0.f) : v;
+            }
+        }
+}
 
 // One operand quad in flight: 4 consecutive elements of a row-major operand
-// (and of its mask) as loaded, plus whether they lie inside the operand.
+// as loaded, plus whether they lie inside the operand.
 // The loads are issued unconditionally (an out-of-range quad reads the
 // operand's first element instead) so that the number of loads in flight is
-// static; the zero fill and the mask are applied only when the quad is
-// written to LDS, so no wait on the loads sits between fetch and compute.
+// static; the zero fill is applied only when the quad is written to LDS, so
+// no wait on the loads sits between fetch and compute.
 // With VEC a quad is one aligned 16-byte load (the row stride is a multiple
 // of 4, so a quad that starts inside a row ends inside its stride); its
 // elements past the extent are zeroed, so padding columns may hold
 // anything, NaN included.
-template <bool VEC, bool MASK>
+template <bool VEC>
 struct Quad {
     float v[4];
-    float m[4];
     uint32_t ok;   // bit j: element j is inside the operand
 
-    __device__ __forceinline__ void load(const float *__restrict__ base,
-                                         const float *__restrict__ mbase, int64_t off, int pos,
+    __device__ __forceinline__ void load(const float *__restrict__ base, int64_t off, int pos,
                                          int lim, bool row_ok)
     {
         if constexpr (VEC) {
@@ -1070,13 +1409,6 @@ struct Quad {
             v[1] = a.y;
             v[2] = a.z;
             v[3] = a.w;
-            if constexpr (MASK) {
-                const float4 b = *reinterpret_cast<const float4 *>(mbase + o);
-                m[0] = b.x;
-                m[1] = b.y;
-                m[2] = b.z;
-                m[3] = b.w;
-            }
             const int left = lim - pos;
             ok = !in ? 0u : left >= 4 ? 0xFu : (1u << left) - 1u;
         } else {
@@ -1086,8 +1418,6 @@ struct Quad {
                 const bool in = row_ok && pos + j < lim;
                 const int64_t o = in ? off + j : 0;
                 v[j] = base[o];
-                if constexpr (MASK)
-                    m[j] = mbase[o];
                 ok |= in ? (1u << j) : 0u;
             }
         }
@@ -1095,34 +1425,32 @@ struct Quad {
 
     __device__ __forceinline__ float get(int j) const
     {
-        const bool keep = ((ok >> j) & 1u) && (!MASK || m[j] > 0.f);
-        return keep ? v[j] : 0.f;
+        return (ok >> j) & 1u ? v[j] : 0.f;
     }
 };
 
+// C = A B on the fp32 instructions (v_mfma_f32_32x32x2f32), for the GAT
+// layer's transform: the rounding of z decides on which side of LeakyReLU's
+// kink a score falls, and with it that entry's derivative, so z keeps the
+// summation it has always had; every other product runs on k_gemm.
 // BM x BN tile of C per workgroup; 4 waves in a 2x2 arrangement, each owning
-// (BM/2) x (BN/2) as TM x TN blocks of 32x32 accumulated with
-// v_mfma_f32_32x32x2f32 (the A fragment of a k step is shared by the TN
-// blocks of a row, the B fragment by the TM blocks of a column).  K advances
-// BK = 32 at a time through two LDS buffers ([k][m] and [k][n], so that the
-// fragment read of lane l -- row l%32 at k = l/32 -- is contiguous); the two
-// following K tiles are in flight in registers while the current one is
-// multiplied; one barrier per K step.
-template <int BM, int BN, bool AT, bool BT, bool AMASK, bool BMASK, bool RELU, bool VA, bool VB>
-__global__ __launch_bounds__(256) void k_gemm(int32_t M, int32_t N, int32_t K, int32_t kchunk,
-                                              const float *__restrict__ A, int32_t lda,
-                                              const float *__restrict__ Am,
-                                              const float *__restrict__ B, int32_t ldb,
-                                              const float *__restrict__ Bm,
-                                              float *__restrict__ C, int32_t ldc,
-                                              int64_t c_split_stride, int32_t gm, int32_t gn)
+// (BM/2) x (BN/2) as TM x TN blocks of 32x32 (the A fragment of a k step is
+// shared by the TN blocks of a row, the B fragment by the TM blocks of a
+// column).  K advances BK = 32 at a time through two LDS buffers ([k][m] and
+// [k][n], so that the fragment read of lane l -- row l%32 at k = l/32 -- is
+// contiguous); the two following K tiles are in flight in registers while
+// the current one is multiplied; one barrier per K step.
+template <int BM, int BN, bool VA, bool VB>
+__global__ __launch_bounds__(256) void k_gemm_f32(int32_t M, int32_t N, int32_t K,
+                                                  const float *__restrict__ A, int32_t lda,
+                                                  const float *__restrict__ B, int32_t ldb,
+                                                  float *__restrict__ C, int32_t ldc, int32_t gn)
 {
     constexpr int BK = kGemmBK;
     constexpr int TM = BM / 64, TN = BN / 64;     // 32x32 blocks per wave
     constexpr int QA = BM * BK / 4 / 256;         // operand quads per thread
     constexpr int QB = BN * BK / 4 / 256;
-    constexpr int PA = AT ? 4 : 1;   // [k][m] rows written as float4 when m is contiguous
-    constexpr int PB = BT ? 1 : 4;
+    constexpr int PA = 1, PB = 4;   // [k][n] rows are written as float4
     static_assert(BK == 32 && (BM == 64 || BM == 128) && (BN == 64 || BN == 128), "tile");
     __shared__ float As[2][BK][BM + PA];
     __shared__ float Bs[2][BK][BN + PB];
@@ -1130,16 +1458,10 @@ __global__ __launch_bounds__(256) void k_gemm(int32_t M, int32_t N, int32_t K, i
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wid = tid / kWave;
-    // Logical tiles: split-major, then M strip, then N tile, so that an XCD
-    // holds whole K slices and the N tiles of an M strip (shared operands).
-    const uint32_t logical = xcd_contiguous(blockIdx.x, gridDim.x);
-    const uint32_t per_split = (uint32_t)gm * (uint32_t)gn;
-    const int z = (int)(logical / per_split);
-    const uint32_t t = logical % per_split;
+    // M strip, then N tile, in contiguous runs per XCD (shared operands)
+    const uint32_t t = xcd_contiguous(blockIdx.x, gridDim.x);
     const int m0 = (int)(t / (uint32_t)gn) * BM;
     const int n0 = (int)(t % (uint32_t)gn) * BN;
-    const int kb = z * kchunk;
-    const int ke = min(K, kb + kchunk);
     const int wm = (wid >> 1) * (BM / 2);
     const int wn = (wid & 1) * (BN / 2);
 
@@ -1152,62 +1474,39 @@ __global__ __launch_bounds__(256) void k_gemm(int32_t M, int32_t N, int32_t K, i
             for (int e = 0; e < 16; ++e)
                 acc[i][j][e] = 0.f;
 
-    using QAt = Quad<VA, AMASK>;
-    using QBt = Quad<VB, BMASK>;
+    using QAt = Quad<VA>;
+    using QBt = Quad<VB>;
     QAt qa0[QA], qa1[QA];
     QBt qb0[QB], qb1[QB];
     auto fetch = [&](int k0, QAt (&qa)[QA], QBt (&qb)[QB]) {
 #pragma unroll
         for (int i = 0; i < QA; ++i) {
             const int q = tid + 256 * i;
-            if (AT) {   // A(m,k) = A[k*lda + m]; quad along m
-                const int k = q / (BM / 4), m = (q % (BM / 4)) * 4;
-                qa[i].load(A, Am, (int64_t)(k0 + k) * lda + (m0 + m), m0 + m, M, k0 + k < ke);
-            } else {    // A(m,k) = A[m*lda + k]; quad along k
-                const int m = q / (BK / 4), k = (q % (BK / 4)) * 4;
-                qa[i].load(A, Am, (int64_t)(m0 + m) * lda + (k0 + k), k0 + k, ke, m0 + m < M);
-            }
+            const int m = q / (BK / 4), k = (q % (BK / 4)) * 4;
+            qa[i].load(A, (int64_t)(m0 + m) * lda + (k0 + k), k0 + k, K, m0 + m < M);
         }
 #pragma unroll
         for (int i = 0; i < QB; ++i) {
             const int q = tid + 256 * i;
-            if (BT) {   // B(k,n) = B[n*ldb + k]; quad along k
-                const int n = q / (BK / 4), k = (q % (BK / 4)) * 4;
-                qb[i].load(B, Bm, (int64_t)(n0 + n) * ldb + (k0 + k), k0 + k, ke, n0 + n < N);
-            } else {    // B(k,n) = B[k*ldb + n]; quad along n
-                const int k = q / (BN / 4), n = (q % (BN / 4)) * 4;
-                qb[i].load(B, Bm, (int64_t)(k0 + k) * ldb + (n0 + n), n0 + n, N, k0 + k < ke);
-            }
+            const int k = q / (BN / 4), n = (q % (BN / 4)) * 4;
+            qb[i].load(B, (int64_t)(k0 + k) * ldb + (n0 + n), n0 + n, N, k0 + k < K);
         }
     };
     auto stash = [&](int buf, const QAt (&qa)[QA], const QBt (&qb)[QB]) {
 #pragma unroll
         for (int i = 0; i < QA; ++i) {
             const int q = tid + 256 * i;
-            if (AT) {
-                const int k = q / (BM / 4), m = (q % (BM / 4)) * 4;
-                *reinterpret_cast<float4 *>(&As[buf][k][m]) =
-                    make_float4(qa[i].get(0), qa[i].get(1), qa[i].get(2), qa[i].get(3));
-            } else {
-                const int m = q / (BK / 4), k = (q % (BK / 4)) * 4;
+            const int m = q / (BK / 4), k = (q % (BK / 4)) * 4;
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    As[buf][k + j][m] = qa[i].get(j);
-            }
+            for (int j = 0; j < 4; ++j)
+                As[buf][k + j][m] = qa[i].get(j);
         }
 #pragma unroll
         for (int i = 0; i < QB; ++i) {
             const int q = tid + 256 * i;
-            if (BT) {
-                const int n = q / (BK / 4), k = (q % (BK / 4)) * 4;
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    Bs[buf][k + j][n] = qb[i].get(j);
-            } else {
-                const int k = q / (BN / 4), n = (q % (BN / 4)) * 4;
-                *reinterpret_cast<float4 *>(&Bs[buf][k][n]) =
-                    make_float4(qb[i].get(0), qb[i].get(1), qb[i].get(2), qb[i].get(3));
-            }
+            const int k = q / (BN / 4), n = (q % (BN / 4)) * 4;
+            *reinterpret_cast<float4 *>(&Bs[buf][k][n]) =
+                make_float4(qb[i].get(0), qb[i].get(1), qb[i].get(2), qb[i].get(3));
         }
     };
     auto compute = [&](int buf) {
@@ -1235,15 +1534,15 @@ __global__ __launch_bounds__(256) void k_gemm(int32_t M, int32_t N, int32_t K, i
     // set while tile t+2 is requested into the other.  The loop body is
     // straight-line (tiles past the end load as zeros and add nothing), so
     // the compiler can wait on exactly the older register set.
-    const int ntiles = ke > kb ? (ke - kb + BK - 1) / BK : 0;
+    const int ntiles = (K + BK - 1) / BK;
     if (ntiles > 0) {
-        fetch(kb, qa0, qb0);
+        fetch(0, qa0, qb0);
         stash(0, qa0, qb0);
-        fetch(kb + BK, qa1, qb1);
+        fetch(BK, qa1, qb1);
     }
     __syncthreads();
-    for (int t = 0; t < ntiles; t += 2) {
-        const int k0 = kb + t * BK;
+    for (int i = 0; i < ntiles; i += 2) {
+        const int k0 = i * BK;
         fetch(k0 + 2 * BK, qa0, qb0);
         compute(0);
         stash(1, qa1, qb1);
@@ -1254,7 +1553,6 @@ __global__ __launch_bounds__(256) void k_gemm(int32_t M, int32_t N, int32_t K, i
         __syncthreads();
     }
 
-    float *Cz = C + (int64_t)z * c_split_stride;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -1263,12 +1561,8 @@ __global__ __launch_bounds__(256) void k_gemm(int32_t M, int32_t N, int32_t K, i
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int r = m0 + wm + 32 * i + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-                if (r < M && cn < N) {
-                    float v = acc[i][j][e];
-                    if (RELU)
-                        v = fmaxf(v, 0.f);
-                    Cz[(int64_t)r * ldc + cn] = v;
-                }
+                if (r < M && cn < N)
+                    C[(int64_t)r * ldc + cn] = acc[i][j][e];
             }
         }
 }
@@ -2535,50 +2829,53 @@ hipError_t spmm_v(int vec, int gl, int nch, const SpmmBlock *blocks, int32_t n_b
     }
 }
 
-template <int BM, int BN, bool AT, bool BT, bool AMASK, bool BMASK, bool RELU, bool VA, bool VB>
+template <int B, int DEPTH, bool AT, bool BT, bool AMASK, bool BMASK, bool RELU>
 hipError_t gemm_t(const GemmArgs &a, hipStream_t s)
 {
-    const int64_t gm = (a.M + BM - 1) / BM, gn = (a.N + BN - 1) / BN;
+    const int64_t gm = (a.M + B - 1) / B, gn = (a.N + B - 1) / B;
     const int64_t grid = gm * gn * a.splits;
     if (grid > 0x7fffffff)
         return hipErrorInvalidConfiguration;
     const int64_t split_stride = a.splits > 1 ? (int64_t)a.M * a.ldc : 0;
-    hipLaunchKernelGGL((k_gemm<BM, BN, AT, BT, AMASK, BMASK, RELU, VA, VB>), dim3((unsigned)grid),
+    hipLaunchKernelGGL((k_gemm<B, DEPTH, AT, BT, AMASK, BMASK, RELU>), dim3((unsigned)grid),
                        dim3(256), 0, s, a.M, a.N, a.K, a.kchunk, a.A, a.lda, a.a_mask, a.B, a.ldb,
                        a.b_mask, a.C, a.ldc, split_stride, (int32_t)gm, (int32_t)gn);
     return hipGetLastError();
 }
 
-template <bool AT, bool BT, bool AMASK, bool BMASK, bool RELU, bool VA, bool VB>
-hipError_t gemm_tile(const GemmArgs &a, hipStream_t s)
+template <int B, bool VA, bool VB>
+hipError_t gemm_f32_t(const GemmArgs &a, hipStream_t s)
 {
-    switch (a.tile) {
-    case 1: return gemm_t<64, 128, AT, BT, AMASK, BMASK, RELU, VA, VB>(a, s);
-    case 2: return gemm_t<128, 64, AT, BT, AMASK, BMASK, RELU, VA, VB>(a, s);
-    case 3: return gemm_t<128, 128, AT, BT, AMASK, BMASK, RELU, VA, VB>(a, s);
-    default: return gemm_t<64, 64, AT, BT, AMASK, BMASK, RELU, VA, VB>(a, s);
-    }
+    const int64_t gm = (a.M + B - 1) / B, gn = (a.N + B - 1) / B;
+    if (gm * gn > 0x7fffffff)
+        return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((k_gemm_f32<B, B, VA, VB>), dim3((unsigned)(gm * gn)), dim3(256), 0, s, a.M,
+                       a.N, a.K, a.A, a.lda, a.B, a.ldb, a.C, a.ldc, (int32_t)gn);
+    return hipGetLastError();
 }
 
-// 16-byte operand loads need a 16-byte aligned base (and mask) and a leading
-// dimension that keeps every row 16-byte aligned.
-bool quad_ok(const float *p, const float *mask, int32_t ld)
+template <int B>
+hipError_t gemm_f32(const GemmArgs &a, hipStream_t s)
 {
-    auto al = [](const float *q) { return q == nullptr || ((uintptr_t)q % 16) == 0; };
-    return al(p) && al(mask) && ld % 4 == 0;
+    // 16-byte operand loads need a 16-byte aligned base and leading dimension
+    const bool va = ((uintptr_t)a.A % 16) == 0 && a.lda % 4 == 0;
+    const bool vb = ((uintptr_t)a.B % 16) == 0 && a.ldb % 4 == 0;
+    if (va && vb)
+        return gemm_f32_t<B, true, true>(a, s);
+    if (va)
+        return gemm_f32_t<B, true, false>(a, s);
+    return vb ? gemm_f32_t<B, false, true>(a, s) : gemm_f32_t<B, false, false>(a, s);
 }
 
+// The 128x128 tile leaves registers for one tile in flight, the 64x64 tile
+// for two (a third or fourth made it slower).
 template <bool AT, bool BT, bool AMASK, bool BMASK, bool RELU>
 hipError_t gemm_q(const GemmArgs &a, hipStream_t s)
 {
-    const bool va = quad_ok(a.A, a.a_mask, a.lda), vb = quad_ok(a.B, a.b_mask, a.ldb);
-    if (va && vb)
-        return gemm_tile<AT, BT, AMASK, BMASK, RELU, true, true>(a, s);
-    if (va)
-        return gemm_tile<AT, BT, AMASK, BMASK, RELU, true, false>(a, s);
-    if (vb)
-        return gemm_tile<AT, BT, AMASK, BMASK, RELU, false, true>(a, s);
-    return gemm_tile<AT, BT, AMASK, BMASK, RELU, false, false>(a, s);
+    if constexpr (!AT)   // (the weight gradients' contractions use 64x64 tiles)
+        if (a.tile == 1)
+            return gemm_t<128, 1, AT, BT, AMASK, BMASK, RELU>(a, s);
+    return gemm_t<64, 2, AT, BT, AMASK, BMASK, RELU>(a, s);
 }
 
 }  // namespace
@@ -2841,11 +3138,16 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
 {
     if (a.M <= 0 || a.N <= 0)
         return hipSuccess;
-    if (a.tile < 0 || a.tile > 3)
+    if (a.tile < 0 || a.tile > 1 || (a.tile == 1 && a.a_trans))
         return hipErrorInvalidValue;
     if (a.splits > 1 && a.kchunk % kGemmBK != 0)
-        return hipErrorInvalidValue;   // split starts must stay quad aligned
+        return hipErrorInvalidValue;   // whole K tiles in every split but the last
     const bool am = a.a_mask != nullptr, bm = a.b_mask != nullptr;
+    if (a.f32) {
+        if (a.a_trans || a.b_trans || am || bm || a.relu || a.splits > 1)
+            return hipErrorInvalidValue;
+        return a.tile == 1 ? gemm_f32<128>(a, s) : gemm_f32<64>(a, s);
+    }
     // The instantiations the layer needs:
     //   forward      A.B        (+ReLU epilogue)
     //   dW           A^T.B      (B optionally masked)

@@ -140,7 +140,7 @@ hipError_t launch_relu_mask(int64_t n, int32_t d, const float *g, int32_t ldg, c
 hipError_t launch_transpose(int32_t rows, int32_t cols, const float *src, float *dst,
                             hipStream_t s);
 
-// C = op(A) op(B) in fp32 on MFMA, K-range split into `splits`
+// C = op(A) op(B) in fp32 precision on MFMA, K-range split into `splits`
 // slices (each its own grid part) when splits > 1.
 //   op(A)(m,k) = a_trans ? A[k*lda + m] : A[m*lda + k]      (M x K)
 //   op(B)(k,n) = b_trans ? B[n*ldb + k] : B[k*ldb + n]      (K x N)
@@ -163,7 +163,8 @@ struct GemmArgs {
     bool relu;
     int32_t splits;
     int32_t kchunk;
-    int32_t tile = 0;   // workgroup tile of C: 0 = 64x64, 1 = 64x128, 2 = 128x64, 3 = 128x128
+    int32_t tile = 0;   // workgroup tile of C: 0 = 64x64, 1 = 128x128 (not with a_trans)
+    bool f32 = false;   // multiply on the fp32 instructions (a plain A B only)
 };
 
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t s);
