@@ -317,18 +317,18 @@ digest_status digest_pull_add(digest_partition *p, int32_t level, float *gstore,
  *   alpha   = softmax of e over each row's entries
  *   h_out_i = act(sum_k alpha_ik z_{col k})   (an empty row gives act(0))
  * The GAT calls need a second workspace, bound once after
- * digest_partition_bind_workspace; it keeps z, the scores and alpha of
- * every layer from the forward for the backward.  The GCN calls are
- * unaffected by it.
+ * digest_partition_bind_workspace; it keeps z, the scores, the softmax
+ * statistics and the part of the output from the entries on LeakyReLU's
+ * positive branch of every layer from the forward for the backward.  The
+ * GCN calls are unaffected by it.
  */
 
 /* Bytes of the GAT workspace (256-byte aligned device memory). */
 digest_status digest_gat_query(const digest_partition *p, size_t *workspace_bytes);
 
 /* Bind the GAT workspace (caller-owned device memory, at least the queried
- * size, 256-byte aligned); uploads the transposed-entry permutation and
- * waits for the upload.  Errors: DIGEST_EINVAL, DIGEST_ENOMEM (too small),
- * DIGEST_EHIP. */
+ * size, 256-byte aligned).  Nothing is uploaded.  Errors: DIGEST_EINVAL,
+ * DIGEST_ENOMEM (too small). */
 digest_status digest_gat_bind_workspace(digest_partition *p, void *dev_ptr, size_t bytes,
                                         void *hip_stream);
 
@@ -359,8 +359,10 @@ digest_status digest_gat_forward(digest_partition *p, int32_t layer, const float
  *   dh_in_i  = dz_i W^T (owned rows; NULL skips it)
  *   h_in, h_out, dh_out, w, att: as in and out of the forward of the layer.
  * LeakyReLU'(x) is 1 for x > 0 and negative_slope otherwise (at 0 too), and
- * act' is the ReLU mask h_out > 0.  Sums run in a fixed order (no float
- * atomics).
+ * act' is the ReLU mask h_out > 0.  The row sums of dpre (datt's second
+ * column, dz's target term) come from the forward's sums over LeakyReLU's
+ * positive branch, alpha is formed again from the scores.  Sums run in a
+ * fixed order (no float atomics).
  * Errors: DIGEST_EINVAL, DIGEST_ESTATE (no GAT forward of the layer since
  * the GAT bind, or level layer-1 pulled again since it, pull mode
  * DIGEST_PULL_AGGREGATE with halo nodes), DIGEST_EHIP.

@@ -52,11 +52,8 @@ enum Kind : int32_t {
     K_GAT_SCORES,
     K_GAT_SOFTMAX,
     K_GAT_AGG,
-    K_GAT_EDGE_GRAD,
-    K_GAT_PERM,
-    K_GAT_AGG_T,
-    K_GAT_SCORE_GRAD,
-    K_GAT_SCORE_SUMS,
+    K_GAT_ROWS,
+    K_GAT_ENTRIES,
     K_GAT_DATT,
     K_GAT_DW,
     K_GAT_DGRAD,
@@ -73,8 +70,7 @@ const char *const kKindNames[K_COUNT] = {
     "pull_gather", "push_scatter", "spmm_fwd", "gemm_fwd_relu", "gemm_dw_splitk",
     "splitk_reduce_dw", "gemm_dgrad", "spmm_bwd_transposed", "softmax_xent", "loss_mean",
     "halo_gradient", "grad_push_add", "grad_pull_add", "gat_transform", "gat_scores",
-    "gat_softmax", "gat_aggregate", "gat_edge_grad", "gat_transpose_edges",
-    "gat_aggregate_transposed", "gat_score_grad", "gat_score_sums", "gat_datt", "gat_dw",
+    "gat_softmax", "gat_aggregate", "gat_row_terms", "gat_entry_grad", "gat_datt", "gat_dw",
     "gat_dgrad", "pad_rows", "spmm_gemm_fwd", "spmm_gemm_bwd", "relu_mask", "transpose_w",
     "halo_aggregate", "boundary_rows"};
 
@@ -235,21 +231,23 @@ constexpr int32_t kSliceLong = 2048;
 constexpr int64_t kSliceStrips = 4096;
 constexpr int64_t kSliceRowCost = 32;   // a row's own cost, in entries
 
-int32_t build_slice_blocks(const int32_t *rowptr, int32_t n_rows, std::vector<SpmmBlock> &blocks)
+int32_t build_slice_blocks(const int32_t *rowptr, int32_t n_rows, std::vector<SpmmBlock> &blocks,
+                           int64_t n_strips = kSliceStrips, int64_t min_work = 256,
+                           int32_t long_row = kSliceLong)
 {
     const int64_t total = rowptr[n_rows] - rowptr[0] + kSliceRowCost * n_rows;
-    const int64_t target = std::max<int64_t>(256, total / kSliceStrips);
+    const int64_t target = std::max<int64_t>(min_work, total / n_strips);
     std::vector<SpmmBlock> strips;
     blocks.clear();
     for (int32_t r = 0; r < n_rows;) {
-        if (rowptr[r + 1] - rowptr[r] > kSliceLong) {
+        if (rowptr[r + 1] - rowptr[r] > long_row) {
             blocks.push_back({r, 0, rowptr[r], rowptr[r + 1]});
             ++r;
             continue;
         }
         const int32_t first = r;
         int64_t work = 0;
-        while (r < n_rows && rowptr[r + 1] - rowptr[r] <= kSliceLong &&
+        while (r < n_rows && rowptr[r + 1] - rowptr[r] <= long_row &&
                (r == first || work + rowptr[r + 1] - rowptr[r] + kSliceRowCost <= target)) {
             work += rowptr[r + 1] - rowptr[r] + kSliceRowCost;
             ++r;
@@ -265,6 +263,13 @@ int32_t build_slice_blocks(const int32_t *rowptr, int32_t n_rows, std::vector<Sp
     blocks.insert(blocks.end(), strips.begin(), strips.end());
     return n_long;
 }
+
+// The GAT layer's strips are shorter: its rows cost more each (Reddit-shaped
+// layer of 41 floats: 612 us with 16,384 strips, 530 with 65,536; rows of
+// more than 512 entries given a workgroup each 557).
+constexpr int64_t kGatStrips = 65536;
+constexpr int64_t kGatMinWork = 64;
+constexpr int32_t kGatLong = 2048;
 
 // A tiered plan of one aggregation (one sparse operand at one width).  The
 // source rows (columns of the operand) are ranked by how many entries read
@@ -460,6 +465,9 @@ struct digest_partition {
     // sliced_pays says no)
     std::vector<SpmmBlock> blocks_s_slice, blocks_t_slice;
     int32_t long_s_slice = 0, long_t_slice = 0;
+    // P_m and P_m^T for the GAT layer's passes
+    std::vector<SpmmBlock> blocks_f_gat, blocks_tf_gat;
+    int32_t long_f_gat = 0, long_tf_gat = 0;
     // DIGEST_PULL_ROWS: a pull fills the halo buffer, then S from it;
     // DIGEST_PULL_AGGREGATE: a pull forms S straight from the store and
     // leaves the halo buffer alone (the calls that read it refuse).
@@ -484,6 +492,7 @@ struct digest_partition {
         size_t blocks_f, blocks_t, blocks_tf, blocks_th;
         size_t s_rowptr, s_col, s_val, b_rowptr, b_col, b_gcol, b_val, blocks_s, blocks_b;
         size_t blocks_s_rows, blocks_t_rows, blocks_s_slice, blocks_t_slice;
+        size_t blocks_f_gat, blocks_tf_gat;
         size_t slices;                  // a sliced aggregation's source in column slices
         size_t fuse_order, fuse_order_t;   // per owned row, uint8 (see fuse_order below)
         size_t fz;                      // the fused input gradient's D and long rows
@@ -505,11 +514,9 @@ struct digest_partition {
     std::vector<int64_t> fwd_gen;   // per layer: pull_gen of level layer-1 at forward
 
     // GAT state, in a workspace of its own (digest_gat_bind_workspace)
-    std::vector<int32_t> t_perm;    // entry k of P_m^T is entry t_perm[k] of P_m
     struct GatLayout {
-        size_t t_perm, ones;
-        std::vector<size_t> z, s, alpha;   // per layer 1..L (index 0 unused)
-        size_t alpha_t, dpre, dpre_t, d_o, dz, ds_src, g2, part;
+        std::vector<size_t> z, s, stat, op;   // per layer 1..L (index 0 unused)
+        size_t alpha, d_o, dz, g2, part;
         size_t total;
     } glay{};
     char *gws = nullptr;
@@ -706,6 +713,8 @@ void plan_layout(digest_partition &p)
     l.blocks_t_rows = take(sizeof(SpmmBlock) * p.blocks_t_rows.size());
     l.blocks_s_slice = take(sizeof(SpmmBlock) * p.blocks_s_slice.size());
     l.blocks_t_slice = take(sizeof(SpmmBlock) * p.blocks_t_slice.size());
+    l.blocks_f_gat = take(sizeof(SpmmBlock) * p.blocks_f_gat.size());
+    l.blocks_tf_gat = take(sizeof(SpmmBlock) * p.blocks_tf_gat.size());
     l.blocks_b = take(sizeof(SpmmBlock) * p.blocks_b.size());
     l.halo_buf.assign(p.L, 0);
     l.hagg.assign(p.L, 0);
@@ -776,10 +785,10 @@ void plan_layout(digest_partition &p)
     l.total = o;
 }
 
-// The GAT workspace: the transposed-entry permutation, a column of ones,
-// per layer the transformed rows z, their scores and the attention
-// weights (kept from the forward for the backward), and the backward's
-// scratch, sized for the widest layer.
+// The GAT workspace: per layer the transformed rows z, their scores, the
+// softmax statistics and the positive branch's part of the output (kept from
+// the forward for the backward), and scratch sized for the widest layer.
+// Rows are padded to whole 16-byte vectors.
 void plan_gat_layout(digest_partition &p)
 {
     auto &l = p.glay;
@@ -790,30 +799,28 @@ void plan_gat_layout(digest_partition &p)
         return r;
     };
     const int64_t R = (int64_t)p.n_own + p.n_halo;
-    l.t_perm = take(sizeof(int32_t) * p.nnz);
-    l.ones = take(sizeof(float) * p.n_own);
     l.z.assign(p.L + 1, 0);
     l.s.assign(p.L + 1, 0);
-    l.alpha.assign(p.L + 1, 0);
+    l.stat.assign(p.L + 1, 0);
+    l.op.assign(p.L + 1, 0);
     int64_t dmax = 0, part = 0;
     for (int32_t k = 1; k <= p.L; ++k) {
         const int64_t di = p.widths[k - 1], dout = p.widths[k];
-        l.z[k] = take(sizeof(float) * (size_t)(R * dout));
+        const int64_t ld = padded_width(p.widths[k]);
+        l.z[k] = take(sizeof(float) * (size_t)(R * ld));
         l.s[k] = take(sizeof(float) * (size_t)(R * 2));
-        l.alpha[k] = take(sizeof(float) * (size_t)p.nnz);
-        dmax = std::max(dmax, dout);
+        l.stat[k] = take(sizeof(float) * (size_t)(4 * (int64_t)p.n_own));
+        l.op[k] = take(sizeof(float) * (size_t)(p.n_own * ld));
+        dmax = std::max(dmax, ld);
         const TfPlan t = tf_plan(p.n_own, p.n_halo, di, dout);
         part = std::max<int64_t>(part, (int64_t)t.slices * di * dout);
         int32_t chunk, slices;
         narrow_rows_plan(R, dout, chunk, slices);
         part = std::max<int64_t>(part, (int64_t)slices * dout * 2);
     }
-    l.alpha_t = take(sizeof(float) * p.nnz);
-    l.dpre = take(sizeof(float) * p.nnz);
-    l.dpre_t = take(sizeof(float) * p.nnz);
-    l.d_o = take(sizeof(float) * (size_t)(p.n_own * dmax));
+    l.alpha = take(sizeof(float) * p.nnz);
+    l.d_o = take(sizeof(float) * (size_t)(p.n_own * (dmax + 4)));
     l.dz = take(sizeof(float) * (size_t)(R * dmax));
-    l.ds_src = take(sizeof(float) * (size_t)R);
     l.g2 = take(sizeof(float) * (size_t)(R * 2));
     l.part = take(sizeof(float) * (size_t)part);
     l.total = o;
@@ -936,12 +943,11 @@ digest_status need_bound(const digest_partition *p)
     return DIGEST_OK;
 }
 
-// Sparse aggregation over the local CSR (P_m), the CSR of P_in^T (the first
-// n_own rows of the transpose), of P_m^T (all of it), of P_out^T (its
-// n_halo halo rows, numbered from 0) or of P_s (owned columns, then the
-// halo aggregate's).  `val` replaces the matrix's values (edge weights in
-// the same entry order); relu stores max(x, 0).
-enum class Csr { Fwd, InT, FullT, HaloT, InH };
+// Sparse aggregation over the CSR of P_in^T (the first n_own rows of the
+// transpose), of P_m^T (all of it), of P_out^T (its n_halo halo rows, numbered
+// from 0) or of P_s (owned columns, then the halo aggregate's); relu stores
+// max(x, 0).
+enum class Csr { InT, FullT, HaloT, InH };
 
 // Tiered plans for the aggregations a standard round runs at widths where
 // slicing applies: the forward's P_s at d_in of every aggregate-first layer
@@ -1049,21 +1055,17 @@ digest_status run_spmm(digest_partition *p, Csr which, const float *src0, const 
                        int32_t n_src0, int32_t d, float *out, int32_t layer, hipStream_t s,
                        const digest::SpmmEpilogue *ep = nullptr, int32_t kind = -1,
                        float *out1 = nullptr, int32_t n_out0 = INT32_MAX,
-                       const float *val = nullptr, bool relu = false,
-                       const digest::SpmmRank1 *r1 = nullptr, int32_t lds = 0,
-                       int32_t out_ld = 0, int32_t out_w = 0)
+                       bool relu = false, int32_t lds = 0, int32_t out_ld = 0,
+                       int32_t out_w = 0)
 {
-    if (which == Csr::InT && !ep && !val && !relu && !out1 && !(r1 && r1->a) && kind < 0 &&
+    if (which == Csr::InT && !ep && !relu && !out1 && kind < 0 &&
         !find_tiers(*p, which, d) && sliced_pays(*p, d))
         return run_sliced(p, which, src0, lds > 0 ? lds : d, nullptr, 0, nullptr, 0,
                           out_w > 0 ? out_w : d, out, out_ld > 0 ? out_ld : d, false, layer, s);
-    const bool fwd = which == Csr::Fwd;
-    const std::vector<SpmmBlock> *blocks = &p->blocks_f;
-    size_t boff = p->lay.blocks_f;
-    int32_t n_long = p->long_f;
-    size_t o_rowptr = fwd ? p->lay.rowptr : p->lay.t_rowptr;
-    size_t o_col = fwd ? p->lay.col : p->lay.t_src;
-    size_t o_val = fwd ? p->lay.val : p->lay.t_val;
+    const std::vector<SpmmBlock> *blocks = &p->blocks_tf;
+    size_t boff = p->lay.blocks_tf;
+    int32_t n_long = p->long_tf;
+    size_t o_rowptr = p->lay.t_rowptr, o_col = p->lay.t_src, o_val = p->lay.t_val;
     const bool narrow = d <= digest::kNarrowWide;
     if (which == Csr::InH) {
         blocks = &p->blocks_s, boff = narrow ? p->lay.blocks_s_rows : p->lay.blocks_s;
@@ -1072,18 +1074,15 @@ digest_status run_spmm(digest_partition *p, Csr which, const float *src0, const 
     } else if (which == Csr::InT) {
         blocks = &p->blocks_t, boff = narrow ? p->lay.blocks_t_rows : p->lay.blocks_t;
         n_long = p->long_t;
-    } else if (which == Csr::FullT) {
-        blocks = &p->blocks_tf, boff = p->lay.blocks_tf, n_long = p->long_tf;
     } else if (which == Csr::HaloT) {
         blocks = &p->blocks_th, boff = p->lay.blocks_th, n_long = p->long_th;
     }
     const int32_t *rowptr = p->at<int32_t>(o_rowptr);
     if (which == Csr::HaloT)
         rowptr += p->n_own;
-    Timed t(p, kind >= 0 ? kind : (fwd || which == Csr::InH ? K_SPMM_FWD : K_SPMM_BWD), layer,
-            s);
+    Timed t(p, kind >= 0 ? kind : (which == Csr::InH ? K_SPMM_FWD : K_SPMM_BWD), layer, s);
     const TierPlan *tp = find_tiers(*p, which, d);
-    if (tp && !ep && !val && !relu && !(r1 && r1->a) && n_out0 == INT32_MAX && !out1 &&
+    if (tp && !ep && !relu && n_out0 == INT32_MAX && !out1 &&
         (lds == 0 || lds == d) && (out_ld == 0 || out_ld == d) && (out_w == 0 || out_w == d) &&
         digest::spmm_sliced_ok(d, src0, src1, out)) {
         // sliced passes over the tiers, then the rest, each adding into out
@@ -1102,7 +1101,7 @@ digest_status run_spmm(digest_partition *p, Csr which, const float *src0, const 
                                                  n_src0, n_rows, d, out, c > 0, s)
                     : digest::launch_spmm(b, tp->blk_cnt[c], tp->blk_long[c], rp, tcol, tval,
                                           src0, src1, n_src0, d, out, s, nullptr, nullptr,
-                                          INT32_MAX, false, nullptr, true);
+                                          INT32_MAX, false, true);
             if (digest_status st = hip_check(e, "tiered spmm"))
                 return st;
         }
@@ -1110,9 +1109,8 @@ digest_status run_spmm(digest_partition *p, Csr which, const float *src0, const 
     }
     return hip_check(
         digest::launch_spmm(p->at<SpmmBlock>(boff), (int32_t)blocks->size(), n_long, rowptr,
-                            p->at<int32_t>(o_col), val ? val : p->at<float>(o_val), src0, src1,
-                            n_src0, d, out, s, ep, out1, n_out0, relu, r1, false, lds, out_ld,
-                            out_w),
+                            p->at<int32_t>(o_col), p->at<float>(o_val), src0, src1,
+                            n_src0, d, out, s, ep, out1, n_out0, relu, false, lds, out_ld, out_w),
         "spmm");
 }
 
@@ -1144,7 +1142,7 @@ digest_status halo_aggregate(digest_partition *p, int32_t level, hipStream_t s,
         return hip_check(digest::launch_spmm(blocks, nb, p->long_b, rowptr,
                                              p->at<int32_t>(p->lay.b_gcol), val, store, nullptr,
                                              INT32_MAX, d, out, s, nullptr, nullptr, INT32_MAX,
-                                             false, nullptr, false, d, lw, d),
+                                             false, false, d, lw, d),
                          "halo aggregate");
     return hip_check(digest::launch_spmm(blocks, nb, p->long_b, rowptr,
                                          p->at<int32_t>(p->lay.b_col), val,
@@ -1312,14 +1310,12 @@ digest_status digest_partition_create(int64_t n_global, const int64_t *indptr,
         p->nnz_in = p->t_rowptr[n_owned];
         p->t_src.resize(nnz);
         p->t_val.resize(nnz);
-        p->t_perm.resize(nnz);
         std::vector<int32_t> next(p->t_rowptr.begin(), p->t_rowptr.end() - 1);
         for (int32_t i = 0; i < (int32_t)n_owned; ++i)
             for (int32_t k = p->rowptr[i]; k < p->rowptr[i + 1]; ++k) {
                 const int32_t c = p->col[k];
                 p->t_src[next[c]] = i;
                 p->t_val[next[c]] = p->val[k];
-                p->t_perm[next[c]] = k;
                 ++next[c];
             }
 
@@ -1378,6 +1374,10 @@ digest_status digest_partition_create(int64_t n_global, const int64_t *indptr,
                     build_slice_blocks(p->t_rowptr.data(), p->n_own, p->blocks_t_slice);
                 break;
             }
+        p->long_f_gat = build_slice_blocks(p->rowptr.data(), p->n_own, p->blocks_f_gat,
+                                           kGatStrips, kGatMinWork, kGatLong);
+        p->long_tf_gat = build_slice_blocks(p->t_rowptr.data(), p->n_own + p->n_halo,
+                                            p->blocks_tf_gat, kGatStrips, kGatMinWork, kGatLong);
         plan_tiers(*p);
         plan_layout(*p);
         plan_gat_layout(*p);
@@ -1479,6 +1479,8 @@ digest_status digest_partition_bind_workspace(digest_partition *p, void *dev_ptr
         {l.blocks_s_rows, p->blocks_s_rows.data(), sizeof(SpmmBlock) * p->blocks_s_rows.size()},
         {l.blocks_t_rows, p->blocks_t_rows.data(), sizeof(SpmmBlock) * p->blocks_t_rows.size()},
         {l.blocks_b, p->blocks_b.data(), sizeof(SpmmBlock) * p->blocks_b.size()},
+        {l.blocks_f_gat, p->blocks_f_gat.data(), sizeof(SpmmBlock) * p->blocks_f_gat.size()},
+        {l.blocks_tf_gat, p->blocks_tf_gat.data(), sizeof(SpmmBlock) * p->blocks_tf_gat.size()},
         {l.blocks_s_slice, p->blocks_s_slice.data(),
          sizeof(SpmmBlock) * p->blocks_s_slice.size()},
         {l.blocks_t_slice, p->blocks_t_slice.data(),
@@ -1681,7 +1683,7 @@ digest_status digest_layer_forward(digest_partition *p, int32_t layer, const flo
                 return st;
         } else if (digest_status st = run_spmm(p, Csr::InH, T, nullptr, p->n_own + p->n_bnd, ldt,
                                         h_out, layer, s, nullptr, -1, nullptr, INT32_MAX,
-                                        nullptr, act == DIGEST_ACT_RELU, nullptr, ldt, d_out,
+                                        act == DIGEST_ACT_RELU, ldt, d_out,
                                         d_out))
             return st;
     } else if (p->n_own > 0) {
@@ -1932,14 +1934,14 @@ digest_status backward_transform_first(digest_partition *p, int32_t layer, const
     if (!sliced)
         if (digest_status st = run_spmm(p, Csr::InT, src, nullptr, p->n_own, dg, G, layer, s,
                                         fused_dh ? &ep : nullptr, -1, nullptr, INT32_MAX,
-                                        nullptr, false, nullptr, lsrc, ldg, dg))
+                                        false, lsrc, ldg, dg))
             return st;
     if (dh_halo) {
         // G_halo = P_out^T D; dh_halo = G_halo W^T (in the same launch when
         // the epilogue applies)
         if (digest_status st = run_spmm(p, Csr::HaloT, src, nullptr, p->n_own, dg, G2, layer, s,
                                         fused_dh ? &ep_halo : nullptr, K_HALO_GRAD, nullptr,
-                                        INT32_MAX, nullptr, false, nullptr, lsrc, ldg, dg))
+                                        INT32_MAX, false, lsrc, ldg, dg))
             return st;
         if (!fused_dh) {
             Timed tm(p, K_HALO_GRAD, layer, s);
@@ -2409,26 +2411,8 @@ digest_status digest_gat_bind_workspace(digest_partition *p, void *dev_ptr, size
     if (bytes < p->glay.total)
         return fail(DIGEST_ENOMEM, "GAT workspace has %zu bytes, needs %zu", bytes,
                     p->glay.total);
-    hipStream_t s = (hipStream_t)hip_stream;
-    char *ws = (char *)dev_ptr;
-    if (p->nnz > 0)
-        if (digest_status st = hip_check(
-                hipMemcpyAsync(ws + p->glay.t_perm, p->t_perm.data(), sizeof(int32_t) * p->nnz,
-                               hipMemcpyHostToDevice, s),
-                "GAT upload"))
-            return st;
-    if (p->n_own > 0) {
-        const std::vector<float> ones((size_t)p->n_own, 1.0f);
-        if (digest_status st = hip_check(
-                hipMemcpyAsync(ws + p->glay.ones, ones.data(), sizeof(float) * p->n_own,
-                               hipMemcpyHostToDevice, s),
-                "GAT upload"))
-            return st;
-        // the host vector dies here: wait for the copy
-        if (digest_status st = hip_check(hipStreamSynchronize(s), "GAT upload"))
-            return st;
-    }
-    p->gws = ws;
+    (void)hip_stream;   // nothing is uploaded: every array is written before it is read
+    p->gws = (char *)dev_ptr;
     std::fill(p->gat_done.begin(), p->gat_done.end(), 0);
     return DIGEST_OK;
 }
@@ -2461,18 +2445,19 @@ digest_status digest_gat_forward(digest_partition *p, int32_t layer, const float
     const int32_t R = p->n_own + p->n_halo;
     float *Z = p->gat<float>(p->glay.z[layer]);
     float *S = p->gat<float>(p->glay.s[layer]);
-    float *alpha = p->gat<float>(p->glay.alpha[layer]);
+    float *alpha = p->gat<float>(p->glay.alpha);
+    const int32_t ld = padded_width(d_out);
     {
         Timed t(p, K_GAT_TRANSFORM, layer, s);
-        if (digest_status st = transform_rows(p, layer, h_in, halo, p->n_halo, w, Z,
-                                              p->widths[layer], s, true))
+        if (digest_status st =
+                transform_rows(p, layer, h_in, halo, p->n_halo, w, Z, ld, s, true))
             return st;
     }
     {
         // scores: S = Z att, [R][2] (source, target)
         Timed t(p, K_GAT_SCORES, layer, s);
         if (digest_status st = hip_check(
-                digest::launch_narrow_n(R, R, d_out, 2, Z, nullptr, d_out, att, S, 2, false, s),
+                digest::launch_narrow_n(R, R, d_out, 2, Z, nullptr, ld, att, S, 2, false, s),
                 "GAT scores"))
             return st;
     }
@@ -2482,13 +2467,20 @@ digest_status digest_gat_forward(digest_partition *p, int32_t layer, const float
             if (digest_status st = hip_check(
                     digest::launch_gat_softmax(p->n_own, p->at<int32_t>(p->lay.rowptr),
                                                p->at<int32_t>(p->lay.col), S, negative_slope,
-                                               alpha, s),
+                                               alpha, p->gat<float>(p->glay.stat[layer]), s),
                     "GAT softmax"))
                 return st;
         }
-        if (digest_status st = run_spmm(p, Csr::Fwd, Z, nullptr, R, d_out, h_out, layer, s,
-                                        nullptr, K_GAT_AGG, nullptr, INT32_MAX, alpha,
-                                        act == DIGEST_ACT_RELU))
+        const bool strips = digest::gat_strips(d_out);
+        Timed t(p, K_GAT_AGG, layer, s);
+        if (digest_status st = hip_check(
+                digest::launch_gat_aggregate(
+                    p->at<SpmmBlock>(strips ? p->lay.blocks_f_gat : p->lay.blocks_f),
+                    strips ? p->long_f_gat : p->long_f,
+                    (int32_t)(strips ? p->blocks_f_gat : p->blocks_f).size(),
+                    p->at<int32_t>(p->lay.rowptr), p->at<int32_t>(p->lay.col), alpha, Z, d_out,
+                    ld, h_out, act == DIGEST_ACT_RELU, p->gat<float>(p->glay.op[layer]), s),
+                "GAT aggregation"))
             return st;
     }
     p->gat_done[layer] = 1;
@@ -2526,59 +2518,37 @@ digest_status digest_gat_backward(digest_partition *p, int32_t layer, const floa
     const float *halo = p->n_halo > 0 ? p->at<float>(p->lay.halo_buf[layer - 1]) : nullptr;
     const float *Z = p->gat<float>(p->glay.z[layer]);
     const float *S = p->gat<float>(p->glay.s[layer]);
-    const float *alpha = p->gat<float>(p->glay.alpha[layer]);
-    float *alpha_t = p->gat<float>(p->glay.alpha_t);
-    float *dpre = p->gat<float>(p->glay.dpre);
-    float *dpre_t = p->gat<float>(p->glay.dpre_t);
+    const int32_t ld = padded_width(d_out);
     float *dO = p->gat<float>(p->glay.d_o);
     float *dz = p->gat<float>(p->glay.dz);
-    float *ds_src = p->gat<float>(p->glay.ds_src);
     float *g2 = p->gat<float>(p->glay.g2);
     float *part = p->gat<float>(p->glay.part);
+    const float slope = p->gat_slope[layer];
     {
-        // dO, the per-edge score gradients and their row sums (g2[i][1])
-        Timed t(p, K_GAT_EDGE_GRAD, layer, s);
+        // dO, what the entries need of their rows, and the owned rows' sums of
+        // score gradients (g2[i][1])
+        Timed t(p, K_GAT_ROWS, layer, s);
         if (digest_status st = hip_check(
-                digest::launch_gat_edge_grad(p->at<SpmmBlock>(p->lay.blocks_f),
-                                             (int32_t)p->blocks_f.size(), d_out,
-                                             p->at<int32_t>(p->lay.rowptr),
-                                             p->at<int32_t>(p->lay.col), alpha, S, Z, h_out,
-                                             dh_out, p->gat_act[layer] == DIGEST_ACT_RELU,
-                                             p->gat_slope[layer], dO, dpre, g2, s),
-                "GAT edge gradient"))
+                digest::launch_gat_rows(p->n_own, d_out, ld, S,
+                                        p->gat<float>(p->glay.stat[layer]),
+                                        p->gat<float>(p->glay.op[layer]), h_out, dh_out,
+                                        p->gat_act[layer] == DIGEST_ACT_RELU, slope, dO, g2, s),
+                "GAT row terms"))
             return st;
     }
     {
-        Timed t(p, K_GAT_PERM, layer, s);
+        // dz over every local row, and the source-score gradients (g2[v][0])
+        const bool strips = digest::gat_strips(d_out);
+        Timed t(p, K_GAT_ENTRIES, layer, s);
         if (digest_status st = hip_check(
-                digest::launch_gather_perm2(p->nnz, p->gat<int32_t>(p->glay.t_perm), alpha, dpre,
-                                            alpha_t, dpre_t, s),
-                "GAT transpose"))
-            return st;
-    }
-    // source-score gradients: column sums of dpre
-    if (digest_status st = run_spmm(p, Csr::FullT, p->gat<float>(p->glay.ones), nullptr,
-                                    p->n_own, 1, ds_src, layer, s, nullptr, K_GAT_SCORE_SUMS,
-                                    nullptr, INT32_MAX, dpre_t))
-        return st;
-    // dz = (alpha-weighted P_m)^T dO over every local row, plus the score
-    // terms ds_src[v] att[:,0] + (owned v) g2[v][1] att[:,1] added in its store
-    {
-        digest::SpmmRank1 r1;
-        r1.a = att;
-        r1.x = ds_src;
-        r1.y = g2;
-        r1.ny = p->n_own;
-        if (digest_status st = run_spmm(p, Csr::FullT, dO, nullptr, p->n_own, d_out, dz, layer,
-                                        s, nullptr, K_GAT_AGG_T, nullptr, INT32_MAX, alpha_t,
-                                        false, &r1))
-            return st;
-    }
-    {
-        // the datt operand [ds_src, row sums of the owned rows]
-        Timed t(p, K_GAT_SCORE_GRAD, layer, s);
-        if (digest_status st = hip_check(
-                digest::launch_gat_score_cols(R, p->n_own, ds_src, g2, s), "GAT score columns"))
+                digest::launch_gat_backward(
+                    p->at<SpmmBlock>(strips ? p->lay.blocks_tf_gat : p->lay.blocks_tf),
+                    strips ? p->long_tf_gat : p->long_tf,
+                    (int32_t)(strips ? p->blocks_tf_gat : p->blocks_tf).size(),
+                    p->at<int32_t>(p->lay.t_rowptr),
+                    p->at<int32_t>(p->lay.t_src), S, Z, dO, att, d_out, ld, slope, p->n_own,
+                    g2, dz, s),
+                "GAT entry gradient"))
             return st;
     }
     {
@@ -2587,7 +2557,7 @@ digest_status digest_gat_backward(digest_partition *p, int32_t layer, const floa
         narrow_rows_plan(R, d_out, chunk, slices);
         Timed t(p, K_GAT_DATT, layer, s);
         if (digest_status st = hip_check(
-                digest::launch_dw_narrow(R, R, d_out, 2, Z, nullptr, d_out, g2, 2, chunk, slices,
+                digest::launch_dw_narrow(R, R, d_out, 2, Z, nullptr, ld, g2, 2, chunk, slices,
                                          part, s),
                 "GAT datt"))
             return st;
@@ -2596,13 +2566,13 @@ digest_status digest_gat_backward(digest_partition *p, int32_t layer, const floa
                 "GAT datt reduce"))
             return st;
     }
-    if (digest_status st = weight_grad_rows(p, layer, h_in, halo, p->n_halo, dz, d_out, part, dw,
-                                            s, K_GAT_DW, K_REDUCE_DW))
+    if (digest_status st = weight_grad_rows(p, layer, h_in, halo, p->n_halo, dz, ld, part, dw, s,
+                                            K_GAT_DW, K_REDUCE_DW))
         return st;
     if (!dh_in || p->n_own == 0)
         return DIGEST_OK;
     Timed t(p, K_GAT_DGRAD, layer, s);
-    return times_wt(p->n_own, d_in, d_out, dz, d_out, w, dh_in, s);
+    return times_wt(p->n_own, d_in, d_out, dz, ld, w, dh_in, s);
 }
 
 digest_status digest_sync_period(int32_t K, int64_t iter, int32_t *do_pull, int32_t *do_push)
@@ -2740,17 +2710,13 @@ digest_status digest_profile_model(const digest_partition *p, int32_t model, dou
             const TfPlan t = tf_plan(p->n_own, p->n_halo, p->widths[l - 1], p->widths[l]);
             put(K_GAT_TRANSFORM, l, 4 * (R * di + di * dout + R * dout), 2 * R * di * dout);
             put(K_GAT_SCORES, l, 4 * (R * dout + 2 * dout + 2 * R), 4 * R * dout);
-            put(K_GAT_SOFTMAX, l, 4 * (n + 1) + 16 * nnz + 4 * n);
-            put(K_GAT_AGG, l, 4 * (n + 1) + 8 * nnz + 4 * R * dout + 4 * n * dout, 0.0, p->nnz);
-            put(K_GAT_EDGE_GRAD, l,
-                4 * (n + 1) + 12 * nnz + 12 * n * dout + 4 * R * dout + 8 * R + 4 * n, 0.0,
-                p->nnz);
-            put(K_GAT_PERM, l, 20 * nnz);
-            put(K_GAT_AGG_T, l,
-                4 * (R + 1) + 8 * nnz + 4 * n * dout + 4 * R * dout + 4 * R + 4 * n + 8 * dout,
+            put(K_GAT_SOFTMAX, l, 4 * (n + 1) + 16 * nnz + 20 * n);
+            put(K_GAT_AGG, l, 4 * (n + 1) + 8 * nnz + 4 * R * dout + 8 * n * dout, 0.0, p->nnz);
+            put(K_GAT_ROWS, l, 16 * n * dout + 40 * n);
+            put(K_GAT_ENTRIES, l,
+                4 * (R + 1) + 4 * nnz + 4 * n * dout + 8 * R * dout + 16 * n + 12 * R + 4 * n +
+                    8 * dout,
                 0.0, p->nnz);
-            put(K_GAT_SCORE_SUMS, l, 4 * (R + 1) + 8 * nnz + 4 * n + 4 * R);
-            put(K_GAT_SCORE_GRAD, l, 8 * R + 4 * nh);
             put(K_GAT_DATT, l, 4 * (R * dout + 2 * R + 2 * dout), 4 * R * dout);
             put(K_GAT_DW, l, 4 * (R * di + R * dout + di * dout), 2 * R * di * dout);
             put(K_REDUCE_DW, l, 4 * (t.slices + 1) * di * dout);

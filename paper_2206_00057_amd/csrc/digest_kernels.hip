@@ -214,7 +214,6 @@ struct SpmmOut {
     float *out1;
     int32_t n0;
     bool relu;      // store max(x, 0)
-    SpmmRank1 r1;   // rank-one terms added first when r1.a is set
     int32_t ld;     // row stride of out0 and out1 (floats)
     bool acc;       // out = out + sum
     int32_t w;      // stored columns
@@ -229,11 +228,6 @@ struct SpmmOut {
     {
         if (acc)
             v += row(r)[f];
-        if (r1.a) {
-            const float xa = r1.x[r];
-            const float yb = r < r1.ny ? r1.y[2 * (int64_t)r + 1] : 0.f;
-            v += xa * r1.a[2 * f] + yb * r1.a[2 * f + 1];
-        }
         return relu ? fmaxf(v, 0.f) : v;
     }
     template <int VEC>
@@ -254,17 +248,10 @@ struct SpmmOut {
             for (int i = 0; i < VEC; ++i)
                 v[i] += prev[i];
         }
-        if (relu || r1.a) {
+        if (relu) {
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) {
-                float t = v[i];
-                if (r1.a) {
-                    const float xa = r1.x[r];
-                    const float yb = r < r1.ny ? r1.y[2 * (int64_t)r + 1] : 0.f;
-                    t += xa * r1.a[2 * (off + i)] + yb * r1.a[2 * (off + i) + 1];
-                }
-                v[i] = relu ? fmaxf(t, 0.f) : t;
-            }
+            for (int i = 0; i < VEC; ++i)
+                v[i] = fmaxf(v[i], 0.f);
         }
         if (whole) {
             store_vec<VEC>(p, v);
@@ -2354,8 +2341,12 @@ constexpr int kGatCache = 4;    // scores a lane keeps between the passes
 
 __device__ __forceinline__ float leaky(float x, float slope) { return x > 0.f ? x : slope * x; }
 
-// alpha[k] = softmax over the entries k of row i of
-// LeakyReLU(s[i][1] + s[col[k]][0]), s [rows][2] (source, target score).
+// |alpha[k]| = softmax over the entries k of row i of
+// LeakyReLU(s[i][1] + s[col[k]][0]), s [rows][2] (source, target score),
+// with the sign bit set where the score sum is not positive (the other
+// branch of LeakyReLU); stat[i] = {the row's maximum, 1 / the sum of
+// exponentials, the sum of the positive branch's weights, 0}, zeros for an
+// empty row: with it the backward forms a weight again from the scores.
 // A wave takes a row and strides over its entries three times (the
 // maximum, the sum of exponentials, the weights), combining its lanes by a
 // fixed butterfly, so results are deterministic.  Each lane keeps its first
@@ -2366,7 +2357,8 @@ __global__ __launch_bounds__(256) void k_gat_softmax(int32_t n_rows,
                                                      const int32_t *__restrict__ rowptr,
                                                      const int32_t *__restrict__ col,
                                                      const float *__restrict__ s, float slope,
-                                                     float *__restrict__ alpha)
+                                                     float *__restrict__ alpha,
+                                                     float4 *__restrict__ stat)
 {
     constexpr int U = kGatCache;
     const int lane = threadIdx.x & (kWave - 1);
@@ -2374,8 +2366,11 @@ __global__ __launch_bounds__(256) void k_gat_softmax(int32_t n_rows,
     if (row >= n_rows)
         return;   // uniform per wave
     const int kb = rowptr[row], ke = rowptr[row + 1];
-    if (ke <= kb)
-        return;   // an empty row has no weights
+    if (ke <= kb) {   // an empty row has no weights
+        if (lane == 0)
+            stat[row] = make_float4(0.f, 0.f, 0.f, 0.f);
+        return;
+    }
     const float t = s[2 * row + 1];
     // scores of entries k0 + lane + u * 64, u < U (-inf past the row); the
     // loads are unconditional (an entry past the row reads its last one)
@@ -2424,11 +2419,19 @@ __global__ __launch_bounds__(256) void k_gat_softmax(int32_t n_rows,
     for (int off = kWave / 2; off > 0; off >>= 1)
         l += __shfl_xor(l, off);
     const float inv = 1.f / l;
+    // e > 0 exactly where the score sum is positive (slope >= 0; at slope 0
+    // the other branch's scores are zeros)
+    float pos = 0.f;
+    auto weight = [&](int k, float e) {
+        const float w = expf(e - m) * inv;
+        pos += e > 0.f ? w : 0.f;
+        alpha[k] = e > 0.f ? w : -w;
+    };
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int k = kb + lane + u * kWave;
         if (k < ke)
-            alpha[k] = expf(ec[u] - m) * inv;
+            weight(k, ec[u]);
     }
     for (int k0 = kb + SPAN; k0 < ke; k0 += SPAN) {
         float e[U];
@@ -2437,190 +2440,350 @@ __global__ __launch_bounds__(256) void k_gat_softmax(int32_t n_rows,
         for (int u = 0; u < U; ++u) {
             const int k = k0 + lane + u * kWave;
             if (k < ke)
-                alpha[k] = expf(e[u] - m) * inv;
-        }
-    }
-}
-
-// Per-edge gradient of the GAT layer over the owned rows i:
-//   D_i     = dh_out_i * 1[h_out_i > 0] (relu) or dh_out_i    -> dO_i
-//   c_i     = D_i . h_out_i  (= D_i . o_i: the mask zeroes D where o <= 0)
-//   dpre[k] = alpha[k] (D_i . z_{col k} - c_i) * LeakyReLU'(t_i + s_{col k})
-//   g2[i][1] = sum_k dpre[k]
-// Work follows the aggregation's block plan: a short-row block gives wave w
-// the row b.row + w; a long-row block splits the entries of row b.row into
-// kSpmmWaves contiguous parts, one per wave, and adds the waves' row sums
-// in LDS in wave order (so a row of thousands of entries is not one wave's
-// serial loop).  Inside a wave the G = 64 / GL lane groups split the
-// entries, U per group in flight at once; inside a group GL lanes hold D_i
-// as NCH vectors of VEC features and gather the matching features of z; the
-// U dot products of a group go through one butterfly together.  All sums
-// have a fixed order.  At most four waves per SIMD: left to maximise
-// occupancy the compiler reuses one register quad for every gather and
-// waits on each, which serialises the step.
-template <int VEC, int GL, int NCH, int U>
-__global__ __launch_bounds__(kSpmmThreads) __attribute__((amdgpu_waves_per_eu(1, 4))) void
-k_gat_edge_grad(const SpmmBlock *__restrict__ blocks, int32_t d,
-                const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
-                const float *__restrict__ alpha, const float *__restrict__ s,
-                const float *__restrict__ z, const float *__restrict__ h_out,
-                const float *__restrict__ dh_out, bool relu, float slope, float *__restrict__ dO,
-                float *__restrict__ dpre, float *__restrict__ g2)
-{
-    constexpr int G = kWave / GL;
-    __shared__ float red[kSpmmWaves];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
-    const int g = lane / GL, gl = lane % GL;
-    const SpmmBlock b = blocks[blockIdx.x];
-    const bool long_row = b.nrows == 0;   // uniform over the block
-    int64_t row;
-    int kb, ke;
-    if (long_row) {
-        row = b.row;
-        const int per = (b.ke - b.kb + kSpmmWaves - 1) / kSpmmWaves;
-        kb = min(b.ke, b.kb + wave * per);
-        ke = min(b.ke, kb + per);
-    } else {
-        if (wave >= b.nrows)
-            return;   // uniform per wave; short-row blocks have no barrier
-        row = b.row + wave;
-        kb = rowptr[row];
-        ke = rowptr[row + 1];
-    }
-    const bool writer = !long_row || wave == 0;   // stores dO and g2
-    const int dv = d / VEC;
-    float D[NCH][VEC];
-    float c = 0.f;
-#pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-        const int cv = ch * GL + gl;
-        if (cv < dv) {
-            float dh[VEC], h[VEC];
-            load_vec<VEC>(dh_out + row * d + cv * VEC, dh);
-            load_vec<VEC>(h_out + row * d + cv * VEC, h);
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                D[ch][v] = (!relu || h[v] > 0.f) ? dh[v] : 0.f;
-                c = fmaf(D[ch][v], h[v], c);
-            }
-            if (writer && g == 0)
-                store_vec<VEC>(dO + row * d + cv * VEC, D[ch]);
-        } else {
-#pragma unroll
-            for (int v = 0; v < VEC; ++v)
-                D[ch][v] = 0.f;
-        }
-    }
-#pragma unroll
-    for (int off = GL / 2; off > 0; off >>= 1)
-        c += __shfl_xor(c, off);
-    const float t = s[2 * row + 1];
-    float rowsum = 0.f;
-    // Every load below is issued unconditionally from a valid address (an
-    // entry past the part reads the part's last entry, a vector past the
-    // width its first vector) and its result is ignored or multiplied by a
-    // zero of D, so all U x NCH gathers of a step are in flight together.
-    for (int k0 = kb; k0 < ke; k0 += G * U) {
-        int kk[U];
-        bool ok[U];
-        int64_t jj[U];
-        float al[U], sj[U], dot[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            kk[u] = k0 + u * G + g;
-            ok[u] = kk[u] < ke;
-            kk[u] = ok[u] ? kk[u] : ke - 1;
-            jj[u] = col[kk[u]];
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            al[u] = alpha[kk[u]];
-            sj[u] = s[2 * jj[u]];
-            dot[u] = 0.f;
-        }
-        float zv[U][NCH][VEC];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int ch = 0; ch < NCH; ++ch) {
-                const int cv = ch * GL + gl < dv ? ch * GL + gl : 0;
-                load_vec<VEC>(z + jj[u] * d + cv * VEC, zv[u][ch]);
-            }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int ch = 0; ch < NCH; ++ch)
-#pragma unroll
-                for (int v = 0; v < VEC; ++v)
-                    dot[u] = fmaf(D[ch][v], zv[u][ch][v], dot[u]);
-#pragma unroll
-        for (int off = GL / 2; off > 0; off >>= 1)
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                dot[u] += __shfl_xor(dot[u], off);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (ok[u]) {
-                const float pre = t + sj[u];
-                const float dp = al[u] * (dot[u] - c) * (pre > 0.f ? 1.f : slope);
-                if (gl == 0) {
-                    dpre[kk[u]] = dp;
-                    rowsum += dp;
-                }
-            }
+                weight(k, e[u]);
         }
     }
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1)
-        rowsum += __shfl_xor(rowsum, off);
-    if (long_row) {
-        if (lane == 0)
-            red[wave] = rowsum;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            float r = 0.f;
-#pragma unroll
-            for (int w = 0; w < kSpmmWaves; ++w)
-                r += red[w];
-            g2[2 * row + 1] = r;
+        pos += __shfl_xor(pos, off);
+    if (lane == 0)
+        stat[row] = make_float4(m, inv, pos, 0.f);
+}
+
+// The backward's row terms, 16 lanes per owned row i:
+//   D_i  = dh_out_i (masked by h_out_i > 0 with relu)  -> dO_i, zeros past d
+//   c_i  = D_i . h_out_i   (= D_i . o_i: the mask zeroes D where o <= 0)
+//   g2[i][1] = sum_k dpre_ik = (1 - slope) (D_i . op_i - c_i pos_i)
+//   rec  = {t_i, maximum, 1 / sum, c_i}, what an entry of row i needs besides
+//          D_i: stored behind it in the same row of dO (columns ld .. ld + 3,
+//          rows ld + 4 apart), so that a gather reads them from its lines
+// The row's sum of score gradients alpha (D . z - c) LeakyReLU' is slope
+// times the sum over all entries, which is c - c = 0, plus (1 - slope) times
+// the sum over the entries of LeakyReLU's positive branch: with op_i the
+// part of o_i from those entries and pos_i their weights (both from the
+// forward) no pass over the entries is needed.
+__global__ __launch_bounds__(256) void k_gat_rows(int32_t n, int32_t d, int32_t ld,
+                                                  const float *__restrict__ s,
+                                                  const float4 *__restrict__ stat,
+                                                  const float *__restrict__ op,
+                                                  const float *__restrict__ h_out,
+                                                  const float *__restrict__ dh_out, bool relu,
+                                                  float slope, float *__restrict__ dO,
+                                                  float *__restrict__ g2)
+{
+    const int64_t r = (int64_t)blockIdx.x * (256 / 16) + threadIdx.x / 16;
+    const int gl = threadIdx.x % 16;
+    if (r >= n)
+        return;   // whole groups; the sums below stay inside a group
+    float c = 0.f, q = 0.f;
+#pragma unroll 4
+    for (int f = gl; f < ld; f += 16) {
+        float D = 0.f;
+        if (f < d) {
+            const float h = h_out[r * d + f];
+            D = !relu || h > 0.f ? dh_out[r * d + f] : 0.f;
+            c = fmaf(D, h, c);
+            q = fmaf(D, op[r * ld + f], q);
         }
-    } else if (lane == 0) {
-        g2[2 * row + 1] = rowsum;
+        dO[r * (ld + 4) + f] = D;
+    }
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) {
+        c += __shfl_xor(c, off);
+        q += __shfl_xor(q, off);
+    }
+    if (gl == 0) {
+        const float4 st = stat[r];
+        const float rec[4] = {s[2 * r + 1], st.x, st.y, c};
+        store_vec<4>(dO + r * (ld + 4) + ld, rec);
+        g2[2 * r + 1] = (1.f - slope) * (q - c * st.z);
     }
 }
 
-// a_t[k] = a[perm[k]], b_t[k] = b[perm[k]]: edge values into the entry order
-// of the transposed CSR.
-__global__ __launch_bounds__(256) void k_gather_perm2(int64_t n, const int32_t *__restrict__ perm,
-                                                      const float *__restrict__ a,
-                                                      const float *__restrict__ b,
-                                                      float *__restrict__ a_t,
-                                                      float *__restrict__ b_t)
+// Sum of x over the caller's group of GL lanes (4 .. 64), in every lane.
+template <int GL>
+__device__ __forceinline__ float group_sum(float x)
 {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < n) {
-        const int32_t p = perm[k];
-        a_t[k] = a[p];
-        b_t[k] = b[p];
+    static_assert(GL == 4 || GL == 8 || GL == 16 || GL == 32 || GL == 64, "lane groups");
+    auto dpp = [](float v, auto ctrl) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v),
+                                                          decltype(ctrl)::value, 0xF, 0xF,
+                                                          false));
+    };
+    x += dpp(x, std::integral_constant<int, 0xB1>{});    // quad_perm [1, 0, 3, 2]
+    x += dpp(x, std::integral_constant<int, 0x4E>{});    // quad_perm [2, 3, 0, 1]
+    if constexpr (GL >= 8)
+        x += dpp(x, std::integral_constant<int, 0x141>{});   // row_half_mirror
+    if constexpr (GL >= 16)
+        x += dpp(x, std::integral_constant<int, 0x128>{});   // row_ror:8
+    if constexpr (GL >= 32) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x),
+                                                        false, false);
+        x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
     }
+    if constexpr (GL == 64) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x),
+                                                        false, false);
+        x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    return x;
 }
 
-// Score terms of the GAT backward over the local rows v < R:
-//   dz[v] += ds_src[v] att[:,0] + (v < n_own ? g2[v][1] att[:,1] : 0)
-//   g2[v][0] = ds_src[v];  g2[v][1] = 0 for the halo rows
-// (g2 then holds the gradient of the scores, [R][2]).  A thread per element
-// of dz; the thread of column 0 writes g2.
-__global__ __launch_bounds__(256) void k_gat_score_cols(int64_t R, int32_t n_own,
-                                                        const float *__restrict__ ds_src,
-                                                        float *__restrict__ g2)
+// What the passes over the GAT layer's entries read and write.  Rows of z,
+// op and dz are ld floats apart (d rounded up to 4, 16-byte aligned); columns
+// d .. ld of src are zero or, in the forward, anything.
+struct GatEntries {
+    const int32_t *rowptr, *col;
+    const float *src;       // gathered rows: z (forward), dO with rec (backward)
+    int32_t lds, ld, d;     // row stride of src, of the others, width
+    // forward
+    const float *alpha;     // signed weights (k_gat_softmax)
+    float *out;             // [rows][d]
+    bool relu, vout;        // vout: rows of out take whole vectors
+    float *op;              // [rows][ld]: the positive branch's part
+    // backward, over the rows v of P_m^T
+    const float *s;         // scores [rows][2]
+    const float *z;
+    const float *att;       // [d][2]
+    float slope;
+    int32_t n_own;
+    float *g2;              // [rows][2]: [v][0] written; [v][1] read (owned) or zeroed
+    float *dz;
+};
+
+// One pass over the entries.  Forward (rows i of P_m, entries k):
+//   out_i = act(sum |alpha_k| z_{col k}),   op_i = the positive alphas' part.
+// Backward (rows v of P_m^T, entries k naming owned rows i = col k):
+//   pre = t_i + s_v,  alpha = exp(LeakyReLU(pre) - max_i) / sum_i
+//   dpre = alpha (D_i . z_v - c_i) LeakyReLU'(pre)
+//   dz_v = sum alpha D_i + (sum dpre) att[:,0] + (owned v) g2[v][1] att[:,1]
+//   g2[v][0] = sum dpre
+// The backward needs D_i . z_v and alpha D_i for the same pairs, so one
+// gather of D_i per entry serves both, with z_v held in registers; no edge
+// value is stored, gathered or transposed.  A pass of its own for the dot
+// products (gathering z rows), one that moved the edge values into
+// transposed order and one that summed them are what this replaces:
+// Reddit-shaped layer of 41 floats (14 M entries) 1,347 -> 460 us, its
+// 256-float one 1,967 -> 1,005, Flickr-shaped 256 floats 94 -> 54 (row terms
+// included).  Bound by the gathered lines (the row terms ride in the D row's
+// own) and, on small partitions, by a row's chain of dependent loads.
+// A lane group of GL lanes holds a row as NCH float4 each and has U entries
+// in flight.  The n_long first blocks are rows whose entries a whole
+// workgroup splits, its waves' sums added in LDS in wave order.  The others,
+// by MODE: kGatGroups, a short-row block (at most 8 rows) per wave, a lane
+// group taking each row (rows of at most 32 floats, where a wave per row
+// would leave most lanes idle: 43,018 rows of mean 21, 4 floats, 183 us);
+// kGatStrips, a strip of consecutive rows per wave (as in k_spmm_slice), its
+// groups splitting a row's entries; kGatWaves, the rows of one workgroup, one
+// per wave.  All sums have a fixed order.
+enum GatMode { kGatGroups, kGatStrips, kGatWaves };
+
+template <int GL, int NCH, int U, bool BWD, int MODE>
+__global__ __launch_bounds__(kSpmmThreads) void
+k_gat_entries(const SpmmBlock *__restrict__ blocks, int32_t n_long, int32_t n_blocks,
+              const GatEntries g)
 {
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= R)
+    constexpr int G = kWave / GL;
+    constexpr int W = NCH * GL * 4;
+    constexpr int ACC = BWD ? 1 : 2;   // sums of a row: dz, or out and op
+    __shared__ __attribute__((aligned(16))) float red[kSpmmWaves][ACC * W + 4];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int grp = lane / GL, gl = lane % GL;
+    const int dv = g.ld / 4;
+    const int32_t wb = (int32_t)blockIdx.x;
+
+    // this workgroup's block: one row for all waves, or this wave's rows
+    const bool long_row = wb < n_long;   // uniform
+    const int32_t bi = long_row || MODE == kGatWaves
+                           ? wb
+                           : n_long + (wb - n_long) * kSpmmWaves + wave;
+    if (bi >= n_blocks)
         return;
-    g2[2 * v] = ds_src[v];
-    if (v >= n_own)
-        g2[2 * v + 1] = 0.f;
+    const SpmmBlock b = blocks[bi];
+    const bool own = MODE == kGatGroups && !long_row;   // a group has its own row
+    int32_t r = b.row, rend = b.row + (long_row ? 1 : b.nrows);
+    if (!long_row && MODE != kGatStrips) {
+        const int32_t first = MODE == kGatWaves ? wave : grp;
+        if (first >= b.nrows)
+            return;   // a whole wave, or whole groups (which share nothing)
+        r += first;
+        rend = r + 1;
+    }
+    for (; r < rend; ++r) {
+        const int64_t row = r;
+        int32_t kb = g.rowptr[r], ke = g.rowptr[r + 1];
+        if (long_row) {
+            const int32_t per = (ke - kb + kSpmmWaves - 1) / kSpmmWaves;
+            kb = min(ke, kb + wave * per);
+            ke = min(ke, kb + per);
+        }
+        float acc[ACC][NCH][4], z[NCH][4];
+        float ds = 0.f, sv = 0.f, dt = 0.f;
+        if constexpr (BWD) {
+            sv = g.s[2 * row];
+            dt = g.g2[2 * row + 1];   // (a halo row's is not used)
+        }
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) {
+            const int cv = ch * GL + gl;
+            if constexpr (BWD)
+                load_vec<4>(g.z + row * g.ld + (cv < dv ? cv : 0) * 4, z[ch]);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                if constexpr (BWD)
+                    z[ch][v] = cv * 4 + v < g.d ? z[ch][v] : 0.f;
+#pragma unroll
+                for (int a = 0; a < ACC; ++a)
+                    acc[a][ch][v] = 0.f;
+            }
+        }
+        for (int32_t k0 = kb; k0 < ke; k0 += own ? U : U * G) {
+            int32_t i[U];
+            bool ok[U];
+            float a[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int32_t k = k0 + (own ? u : u * G + grp);
+                ok[u] = k < ke;
+                const int32_t kc = ok[u] ? k : ke - 1;
+                i[u] = g.col[kc];
+                if constexpr (!BWD)
+                    a[u] = ok[u] ? g.alpha[kc] : 0.f;
+            }
+            float4 rc[U];
+            float x[U][NCH][4];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if constexpr (BWD)
+                    rc[u] = *reinterpret_cast<const float4 *>(g.src + (int64_t)i[u] * g.lds +
+                                                              g.ld);
+#pragma unroll
+                for (int ch = 0; ch < NCH; ++ch) {
+                    const int cv = ch * GL + gl;   // past the width: vector 0 again, not used
+                    load_vec<4>(g.src + (int64_t)i[u] * g.lds + (cv < dv ? cv : 0) * 4, x[u][ch]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if constexpr (BWD) {
+                    float dot = 0.f;   // z is zero past the width
+#pragma unroll
+                    for (int ch = 0; ch < NCH; ++ch)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            dot = fmaf(z[ch][v], x[u][ch][v], dot);
+                    dot = group_sum<GL>(dot);
+                    const float pre = rc[u].x + sv;
+                    a[u] = ok[u] ? expf(leaky(pre, g.slope) - rc[u].y) * rc[u].z : 0.f;
+                    ds += ok[u] ? a[u] * (dot - rc[u].w) * (pre > 0.f ? 1.f : g.slope) : 0.f;
+                }
+                const float w = BWD ? a[u] : fabsf(a[u]);
+                const float wp = fmaxf(a[u], 0.f);
+#pragma unroll
+                for (int ch = 0; ch < NCH; ++ch)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        acc[0][ch][v] = fmaf(w, x[u][ch][v], acc[0][ch][v]);
+                        if constexpr (!BWD)
+                            acc[ACC - 1][ch][v] = fmaf(wp, x[u][ch][v], acc[ACC - 1][ch][v]);
+                    }
+            }
+        }
+        if (!own) {
+#pragma unroll
+            for (int off = GL; off < kWave; off <<= 1) {
+#pragma unroll
+                for (int c = 0; c < ACC; ++c)
+#pragma unroll
+                    for (int ch = 0; ch < NCH; ++ch)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            acc[c][ch][v] += __shfl_xor(acc[c][ch][v], off);
+                if constexpr (BWD)
+                    ds += __shfl_xor(ds, off);
+            }
+        }
+        if (long_row) {
+            if (grp == 0) {
+#pragma unroll
+                for (int c = 0; c < ACC; ++c)
+#pragma unroll
+                    for (int ch = 0; ch < NCH; ++ch)
+                        store_vec<4>(&red[wave][c * W + (ch * GL + gl) * 4], acc[c][ch]);
+                if (gl == 0)
+                    red[wave][ACC * W] = ds;
+            }
+            __syncthreads();
+            if (wave != 0 || grp != 0)
+                return;
+            ds = 0.f;
+#pragma unroll
+            for (int c = 0; c < ACC; ++c)
+#pragma unroll
+                for (int ch = 0; ch < NCH; ++ch)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        acc[c][ch][v] = 0.f;
+            for (int w = 0; w < kSpmmWaves; ++w) {
+#pragma unroll
+                for (int c = 0; c < ACC; ++c)
+#pragma unroll
+                    for (int ch = 0; ch < NCH; ++ch) {
+                        float t[4];
+                        load_vec<4>(&red[w][c * W + (ch * GL + gl) * 4], t);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            acc[c][ch][v] += t[v];
+                    }
+                ds += red[w][ACC * W];
+            }
+        } else if (!own && grp != 0) {
+            continue;
+        }
+        // one group stores the row; loads are unconditional, so that they
+        // are in flight together
+        if constexpr (BWD) {
+            dt = row < g.n_own ? dt : 0.f;
+#pragma unroll
+            for (int ch = 0; ch < NCH; ++ch) {
+                const int cv = ch * GL + gl;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int f = min(cv * 4 + v, g.d - 1);
+                    acc[0][ch][v] += ds * g.att[2 * f] + dt * g.att[2 * f + 1];
+                }
+                if (cv < dv)
+                    store_vec<4>(g.dz + row * g.ld + cv * 4, acc[0][ch]);
+            }
+            if (gl == 0) {
+                g.g2[2 * row] = ds;
+                if (row >= g.n_own)
+                    g.g2[2 * row + 1] = 0.f;
+            }
+        } else {
+#pragma unroll
+            for (int ch = 0; ch < NCH; ++ch) {
+                const int cv = ch * GL + gl;
+                if (cv >= dv)
+                    continue;
+                if (g.relu) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        acc[0][ch][v] = fmaxf(acc[0][ch][v], 0.f);
+                }
+                if (g.vout) {
+                    store_vec<4>(g.out + row * g.d + cv * 4, acc[0][ch]);
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (cv * 4 + v < g.d)
+                            g.out[row * g.d + cv * 4 + v] = acc[0][ch][v];
+                }
+                store_vec<4>(g.op + row * g.ld + cv * 4, acc[ACC - 1][ch]);
+            }
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -2975,7 +3138,7 @@ hipError_t launch_spmm_sliced(const SpmmBlock *blocks, int32_t n_blocks, int32_t
         return hipSuccess;
     if (n_long < 0 || n_long > n_blocks || nnz < 1)
         return hipErrorInvalidValue;   // padding entries reread entry 0
-    const SpmmOut out{out0, nullptr, INT32_MAX, false, SpmmRank1{}, d, acc, d, true};
+    const SpmmOut out{out0, nullptr, INT32_MAX, false, d, acc, d, true};
     // every slice starts on a multiple of kSliceFloats, so the vector width
     // of the whole row is the slices' too
     int vec = pick_vec(d, src0, out0);
@@ -3058,8 +3221,8 @@ hipError_t launch_spmm(const SpmmBlock *blocks, int32_t n_blocks, int32_t n_long
                        const int32_t *rowptr, const int32_t *col, const float *val,
                        const float *src0, const float *src1, int32_t n_src0, int32_t d,
                        float *out0, hipStream_t s, const SpmmEpilogue *ep, float *out1,
-                       int32_t n_out0, bool relu, const SpmmRank1 *r1, bool acc, int32_t lds,
-                       int32_t out_ld, int32_t out_w)
+                       int32_t n_out0, bool relu, bool acc, int32_t lds, int32_t out_ld,
+                       int32_t out_w)
 {
     lds = lds > 0 ? lds : d;
     out_ld = out_ld > 0 ? out_ld : d;
@@ -3073,10 +3236,8 @@ hipError_t launch_spmm(const SpmmBlock *blocks, int32_t n_blocks, int32_t n_long
         return hipErrorInvalidValue;
     if (n_blocks <= 0 || d <= 0)
         return hipSuccess;
-    if ((relu || (r1 && r1->a)) && ep)
+    if (relu && ep)
         return hipErrorInvalidValue;   // the epilogue reads the stored row back
-    if (r1 && r1->a && (!r1->x || (r1->ny > 0 && !r1->y)))
-        return hipErrorInvalidValue;
     // the gather's vector width follows the sources (width, stride and
     // alignment); the stores use it where the output's rows allow, else go
     // column by column
@@ -3086,7 +3247,7 @@ hipError_t launch_spmm(const SpmmBlock *blocks, int32_t n_blocks, int32_t n_long
     if (src1 && pick_vec(d, src1, nullptr) < vec)
         vec = pick_vec(d, src1, nullptr);
     const bool vst = out_ld % vec == 0 && pick_vec(vec, out0, out1) >= vec;
-    const SpmmOut out{out0, out1, n_out0, relu, r1 ? *r1 : SpmmRank1{}, out_ld, acc, out_w, vst};
+    const SpmmOut out{out0, out1, n_out0, relu, out_ld, acc, out_w, vst};
     const int dv = d / vec;
     const int gl = pick_group(dv);
     // rows of at most kNarrowWide floats: the row-per-lane-group kernel, in
@@ -3510,8 +3671,11 @@ hipError_t launch_fill_zero(float *p, int64_t count, hipStream_t s)
     return hipGetLastError();
 }
 
+bool gat_strips(int32_t d) { return d > 32 && d <= 64; }
+
 hipError_t launch_gat_softmax(int32_t n_rows, const int32_t *rowptr, const int32_t *col,
-                              const float *s, float slope, float *alpha, hipStream_t st)
+                              const float *s, float slope, float *alpha, float *stat,
+                              hipStream_t st)
 {
     if (n_rows <= 0)
         return hipSuccess;
@@ -3519,98 +3683,91 @@ hipError_t launch_gat_softmax(int32_t n_rows, const int32_t *rowptr, const int32
     if (blocks > 0x7fffffff)
         return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(k_gat_softmax, dim3((unsigned)blocks), dim3(256), 0, st, n_rows, rowptr,
-                       col, s, slope, alpha);
+                       col, s, slope, alpha, reinterpret_cast<float4 *>(stat));
+    return hipGetLastError();
+}
+
+hipError_t launch_gat_rows(int32_t n, int32_t d, int32_t ld, const float *s, const float *stat,
+                           const float *op, const float *h_out, const float *dh_out, bool relu,
+                           float slope, float *dO, float *g2, hipStream_t st)
+{
+    if (n <= 0)
+        return hipSuccess;
+    hipLaunchKernelGGL(k_gat_rows, dim3((unsigned)(((int64_t)n + 15) / 16)), dim3(256), 0, st, n,
+                       d, ld, s, reinterpret_cast<const float4 *>(stat), op, h_out, dh_out, relu,
+                       slope, dO, g2);
     return hipGetLastError();
 }
 
 namespace {
 
-template <int VEC, int GL, int NCH, int U = 2>
-hipError_t gat_edge_grad_t(const SpmmBlock *blocks, int32_t n_blocks, int32_t d,
-                           const int32_t *rowptr, const int32_t *col, const float *alpha,
-                           const float *s, const float *z, const float *h_out,
-                           const float *dh_out, bool relu, float slope, float *dO, float *dpre,
-                           float *g2, hipStream_t st)
+template <int GL, int NCH, int U, bool BWD, int MODE>
+hipError_t gat_entries_t(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks,
+                         const GatEntries &g, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_gat_edge_grad<VEC, GL, NCH, U>), dim3((unsigned)n_blocks),
-                       dim3(kSpmmThreads), 0, st, blocks, d, rowptr, col, alpha, s, z, h_out,
-                       dh_out, relu, slope, dO, dpre, g2);
+    // a workgroup's waves take a block each, or share one
+    const int64_t grid =
+        MODE == kGatWaves ? n_blocks
+                          : n_long + ((int64_t)(n_blocks - n_long) + kSpmmWaves - 1) / kSpmmWaves;
+    hipLaunchKernelGGL((k_gat_entries<GL, NCH, U, BWD, MODE>), dim3((unsigned)grid),
+                       dim3(kSpmmThreads), 0, st, blocks, n_long, n_blocks, g);
     return hipGetLastError();
+}
+
+template <bool BWD>
+hipError_t gat_entries(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks,
+                       const GatEntries &g, hipStream_t st)
+{
+    if (n_blocks <= 0)
+        return hipSuccess;
+    if (g.d < 1 || g.d > kGatMaxWidth || g.ld < g.d || g.ld % 4 || n_long < 0 ||
+        n_long > n_blocks)
+        return hipErrorInvalidValue;
+    const int dv = g.ld / 4;
+    if (dv <= 4)
+        return gat_entries_t<4, 1, 8, BWD, kGatGroups>(blocks, n_long, n_blocks, g, st);
+    if (dv <= 8)
+        return gat_entries_t<8, 1, 8, BWD, kGatGroups>(blocks, n_long, n_blocks, g, st);
+    if (gat_strips(g.d))
+        return gat_entries_t<8, 2, BWD ? 3 : 4, BWD, kGatStrips>(blocks, n_long, n_blocks, g, st);
+    if (dv <= 32)
+        return gat_entries_t<32, 1, 4, BWD, kGatWaves>(blocks, n_long, n_blocks, g, st);
+    // The backward takes whole waves per entry: fewer registers a lane, so
+    // more waves (Flickr-shaped, 256 floats: 38 us, groups of 32 lanes 52, of
+    // 16 97; 100,000 rows of mean 36: 758, 1,008); the forward, with two
+    // sums a row, is no slower with half as many lanes (60,000 rows of mean
+    // 12: 117, whole waves 156).
+    constexpr int GL = BWD ? 64 : 32;
+    if (dv <= 64)
+        return gat_entries_t<GL, 64 / GL, 4, BWD, kGatWaves>(blocks, n_long, n_blocks, g, st);
+    return gat_entries_t<GL, 128 / GL, 2, BWD, kGatWaves>(blocks, n_long, n_blocks, g, st);
 }
 
 }  // namespace
 
-hipError_t launch_gat_edge_grad(const SpmmBlock *blocks, int32_t n_blocks, int32_t d,
+hipError_t launch_gat_aggregate(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks,
                                 const int32_t *rowptr, const int32_t *col, const float *alpha,
-                                const float *s, const float *z, const float *h_out,
-                                const float *dh_out, bool relu, float slope, float *dO,
-                                float *dpre, float *g2, hipStream_t st)
+                                const float *z, int32_t d, int32_t ld, float *out, bool relu,
+                                float *op, hipStream_t st)
 {
-    if (n_blocks <= 0)
-        return hipSuccess;
-    if (d < 1 || d > kGatMaxWidth)
-        return hipErrorInvalidValue;
-    // vectors of 4/2/1 floats as width and alignment allow; groups of at
-    // most 16 lanes (at least four entries per wave step) up to 128 vectors
-    // per row, whole-wave groups beyond; up to 8 vectors per lane
-    int vec = 1;
-    auto al = [](const void *q, uintptr_t n) { return ((uintptr_t)q % n) == 0; };
-    if (d % 4 == 0 && al(z, 16) && al(h_out, 16) && al(dh_out, 16) && al(dO, 16))
-        vec = 4;
-    else if (d % 2 == 0 && al(z, 8) && al(h_out, 8) && al(dh_out, 8) && al(dO, 8))
-        vec = 2;
-    const int dv = d / vec;
-    const int gl = dv <= 4 ? 4 : (dv <= 8 ? 8 : (dv <= 128 ? 16 : 64));
-    const int nch = (dv + gl - 1) / gl;
-#define DIGEST_GEG(V, L, C)                                                                     \
-    return gat_edge_grad_t<V, L, C>(blocks, n_blocks, d, rowptr, col, alpha, s, z, h_out,       \
-                                    dh_out, relu, slope, dO, dpre, g2, st)
-#define DIGEST_GEG_V(V)                                                                         \
-    do {                                                                                        \
-        if (gl == 4) DIGEST_GEG(V, 4, 1);                                                       \
-        if (gl == 8) DIGEST_GEG(V, 8, 1);                                                       \
-        if (gl == 16) {                                                                         \
-            if (nch <= 1) DIGEST_GEG(V, 16, 1);                                                 \
-            if (nch <= 2) DIGEST_GEG(V, 16, 2);                                                 \
-            if (nch <= 4) DIGEST_GEG(V, 16, 4);                                                 \
-            DIGEST_GEG(V, 16, 8);                                                               \
-        }                                                                                       \
-        if (nch <= 4) DIGEST_GEG(V, 64, 4);                                                     \
-        DIGEST_GEG(V, 64, 8);                                                                   \
-    } while (0)
-    if (vec == 4)
-        DIGEST_GEG_V(4);
-    if (vec == 2)
-        DIGEST_GEG_V(2);
-    DIGEST_GEG_V(1);
-#undef DIGEST_GEG_V
-#undef DIGEST_GEG
+    GatEntries g{};
+    g.rowptr = rowptr, g.col = col, g.src = z, g.lds = ld, g.ld = ld, g.d = d;
+    g.alpha = alpha, g.out = out, g.relu = relu, g.op = op;
+    g.vout = d % 4 == 0 && ((uintptr_t)out % 16) == 0;
+    return gat_entries<false>(blocks, n_long, n_blocks, g, st);
 }
 
-hipError_t launch_gather_perm2(int64_t n, const int32_t *perm, const float *a, const float *b,
-                               float *a_t, float *b_t, hipStream_t st)
+hipError_t launch_gat_backward(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks,
+                               const int32_t *rowptr, const int32_t *col, const float *s,
+                               const float *z, const float *dO, const float *att,
+                               int32_t d, int32_t ld, float slope, int32_t n_own, float *g2,
+                               float *dz, hipStream_t st)
 {
-    if (n <= 0)
-        return hipSuccess;
-    const int64_t blocks = (n + 255) / 256;
-    if (blocks > 0x7fffffff)
-        return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(k_gather_perm2, dim3((unsigned)blocks), dim3(256), 0, st, n, perm, a, b,
-                       a_t, b_t);
-    return hipGetLastError();
-}
-
-hipError_t launch_gat_score_cols(int64_t R, int32_t n_own, const float *ds_src, float *g2,
-                                 hipStream_t st)
-{
-    if (R <= 0)
-        return hipSuccess;
-    const int64_t blocks = (R + 255) / 256;
-    if (blocks > 0x7fffffff)
-        return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(k_gat_score_cols, dim3((unsigned)blocks), dim3(256), 0, st, R, n_own,
-                       ds_src, g2);
-    return hipGetLastError();
+    GatEntries g{};
+    g.rowptr = rowptr, g.col = col, g.src = dO, g.lds = ld + 4, g.ld = ld, g.d = d;
+    g.s = s, g.z = z, g.att = att;
+    g.slope = slope, g.n_own = n_own, g.g2 = g2, g.dz = dz;
+    return gat_entries<true>(blocks, n_long, n_blocks, g, st);
 }
 
 }  // namespace digest

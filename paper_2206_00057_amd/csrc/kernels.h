@@ -56,16 +56,6 @@ struct SpmmEpilogue {
 };
 bool spmm_epilogue_ok(int32_t d, int32_t n2, const float *out2);
 
-// Rank-one terms an aggregation can add to its row r before the store:
-// out[r][f] += x[r] a[f][0] + (r < ny ? y[2r + 1] : 0) a[f][1], with a
-// row-major [d][2] and y [rows][2] (the GAT backward's score terms).
-struct SpmmRank1 {
-    const float *a = nullptr;
-    const float *x = nullptr;
-    const float *y = nullptr;
-    int32_t ny = 0;
-};
-
 // The first n_long blocks are the long-row blocks (nrows == 0), the rest
 // short-row blocks.
 // acc: add each row's sum to what out already holds.  Rows are gathered d
@@ -78,8 +68,8 @@ hipError_t launch_spmm(const SpmmBlock *blocks, int32_t n_blocks, int32_t n_long
                        const float *src0, const float *src1, int32_t n_src0, int32_t d,
                        float *out0, hipStream_t s, const SpmmEpilogue *ep = nullptr,
                        float *out1 = nullptr, int32_t n_out0 = INT32_MAX, bool relu = false,
-                       const SpmmRank1 *r1 = nullptr, bool acc = false, int32_t lds = 0,
-                       int32_t out_ld = 0, int32_t out_w = 0);
+                       bool acc = false, int32_t lds = 0, int32_t out_ld = 0,
+                       int32_t out_w = 0);
 
 // The same aggregation (one output, no epilogue) as one pass over column
 // slices of kSliceFloats floats, the slices dealt to the 8 XCDs so that each
@@ -238,25 +228,36 @@ hipError_t static_scratch(float **ptr);
 hipError_t launch_fill_zero(float *p, int64_t count, hipStream_t s);
 
 // GAT layer (attention aggregation over stale halo rows).  s is [rows][2]
-// (source score, target score); alpha, dpre are in CSR entry order.
+// (source score, target score); alpha is in CSR entry order, its sign bit
+// set where LeakyReLU takes its other branch; stat is four floats per owned
+// row, 16-byte aligned; rows of z, op and dz are ld floats apart (d rounded
+// up to 4, 16-byte aligned).  The blocks list the n_long long-row blocks
+// first, then strips of rows for one wave where gat_strips(d), else runs of
+// at most 8 rows.
 constexpr int kGatMaxWidth = 512;
-// alpha[k] = softmax over row i's entries of LeakyReLU(s[i][1] + s[col k][0]).
+bool gat_strips(int32_t d);
+// |alpha[k]| = softmax over row i's entries of LeakyReLU(s[i][1] + s[col k][0]).
 hipError_t launch_gat_softmax(int32_t n_rows, const int32_t *rowptr, const int32_t *col,
-                              const float *s, float slope, float *alpha, hipStream_t st);
-// dO = dh_out (masked by h_out > 0 with relu), dpre[k] the gradient of the
-// k-th pre-activation score, g2[i][1] = sum of row i's dpre; d <= kGatMaxWidth.
-hipError_t launch_gat_edge_grad(const SpmmBlock *blocks, int32_t n_blocks, int32_t d,
+                              const float *s, float slope, float *alpha, float *stat,
+                              hipStream_t st);
+// out = act(sum |alpha| z) [rows][d]; op: the part with positive alpha.
+hipError_t launch_gat_aggregate(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks,
                                 const int32_t *rowptr, const int32_t *col, const float *alpha,
-                                const float *s, const float *z, const float *h_out,
-                                const float *dh_out, bool relu, float slope, float *dO,
-                                float *dpre, float *g2, hipStream_t st);
-// a_t[k] = a[perm[k]], b_t[k] = b[perm[k]] for k < n.
-hipError_t launch_gather_perm2(int64_t n, const int32_t *perm, const float *a, const float *b,
-                               float *a_t, float *b_t, hipStream_t st);
-// The score-gradient operand of datt: g2[v][0] = ds_src[v] for v < R and
-// g2[v][1] = 0 for n_own <= v < R (the owned rows keep their row sums).
-hipError_t launch_gat_score_cols(int64_t R, int32_t n_own, const float *ds_src, float *g2,
-                                 hipStream_t st);
+                                const float *z, int32_t d, int32_t ld, float *out, bool relu,
+                                float *op, hipStream_t st);
+// The backward's row terms: dO = dh_out (masked by h_out > 0 with relu; its
+// rows are ld + 4 floats apart, the last four for the entries), and g2[i][1]
+// = the row's sum of score gradients.
+hipError_t launch_gat_rows(int32_t n, int32_t d, int32_t ld, const float *s, const float *stat,
+                           const float *op, const float *h_out, const float *dh_out, bool relu,
+                           float slope, float *dO, float *g2, hipStream_t st);
+// dz over the rows v of P_m^T (all local rows), with the score terms, and
+// g2[v][0] = v's sum of score gradients, g2[v][1] = 0 for v >= n_own.
+hipError_t launch_gat_backward(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks,
+                               const int32_t *rowptr, const int32_t *col, const float *s,
+                               const float *z, const float *dO, const float *att,
+                               int32_t d, int32_t ld, float slope, int32_t n_own, float *g2,
+                               float *dz, hipStream_t st);
 
 // GEMM K step; the smallest workgroup tile of C is kGemmBM x kGemmBN.
 constexpr int kGemmBM = 64;
