@@ -565,8 +565,11 @@ namespace {
 // [H_in; S] (its weight gradient runs over them too), gathers nnz_s + nnz_in
 // entries of width d_out (P_s and P_in^T) and copies D's boundary rows; a
 // ReLU layer forms the masked D once, an identity layer pads D when d_out
-// is not a multiple of 4.  The rates are those measured for the aggregation
-// kernels (random row gathers), the fp32 MFMA GEMM and row copies on MI355X.
+// is not a multiple of 4.  The rates are those measured on MI355X for row
+// gathers past the L2, for the GEMM on the fp32 matrix instructions and for
+// row copies.  They were not fitted again when the split GEMM and, on dense
+// partitions, the sliced aggregation made both about twice as fast: the order
+// also decides how results are rounded.
 constexpr double kGatherBytesPerS = 7.0e12;
 constexpr double kGemmFlopsPerS = 80.0e12;
 

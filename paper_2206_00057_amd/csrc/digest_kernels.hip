@@ -12,11 +12,17 @@
 //                  64 at a time and broadcast, many gathers are kept in
 //                  flight, and groups are combined by a butterfly.  Results
 //                  are deterministic; no float atomics, no global fences.
+//   k_spmm_slice   the same aggregation for dense partitions, over sources
+//                  laid out in 128-byte column slices (k_slice_rows) that
+//                  stay in one XCD's L2 each.
 //   k_gemm         GEMM in fp32 precision on the bf16 matrix cores (operands
 //                  split into three bf16) with optional transposed operands,
-//                  ReLU-derivative operand masks, a ReLU epilogue and split-K; tiles are dealt to the XCDs in
-//                  contiguous runs (shared operand strips share an L2): the dense
-//                  transform AH W, the weight gradient AH^T D and D W^T.
+//                  ReLU-derivative operand masks, a ReLU epilogue and
+//                  split-K; tiles are dealt to the XCDs in contiguous runs
+//                  (shared operand strips share an L2): the dense transform
+//                  AH W, the weight gradient AH^T D and D W^T.
+//   k_gemm_f32     the same on the fp32 matrix instructions: the GAT layer's
+//                  transform, whose rounding decides the scores' kink.
 //   k_splitk_reduce  deterministic sum of split-K partial products.
 //   k_narrow_n / k_narrow_k / k_times_wt / k_dw_narrow  products with one
 //                  narrow side (the transform-first last layer).
@@ -24,8 +30,9 @@
 //   k_sgd_average  Algorithm 1's global update: the average of the M
 //                  locally updated models, W - lr * mean of the gradients.
 //   k_gat_*        the GAT layer over stale halo rows (Eq. 4 with an
-//                  attention aggregation): edge softmax, the per-edge
-//                  gradient, and the helpers of its backward.
+//                  attention aggregation): edge softmax, the row terms of
+//                  its backward, and one pass over the transposed entries
+//                  for the score gradients and the gradient's sums.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
