@@ -494,6 +494,7 @@ struct digest_partition {
         size_t blocks_s_rows, blocks_t_rows, blocks_s_slice, blocks_t_slice;
         size_t blocks_f_gat, blocks_tf_gat;
         size_t slices;                  // a sliced aggregation's source in column slices
+        int64_t slices_floats;          // (its size)
         size_t fuse_order, fuse_order_t;   // per owned row, uint8 (see fuse_order below)
         size_t fz;                      // the fused input gradient's D and long rows
         size_t wt;                      // W^T of the fused input gradient
@@ -668,6 +669,9 @@ TfPlan tf_plan(int64_t n_own, int64_t n2, int64_t d_in, int64_t d_out)
 constexpr int64_t kSliceMaxRows = 65536;
 constexpr int32_t kSliceMinWidth = 40;
 
+// d is a layer's own width, never one padded to whole vectors: the lists and
+// the slices are planned by the layers' widths, and a padded width may lie on
+// the other side of a line.  The layer calls ask use_sliced.
 bool sliced_pays(const digest_partition &p, int32_t d)
 {
     const int64_t n = p.n_own;
@@ -677,6 +681,13 @@ bool sliced_pays(const digest_partition &p, int32_t d)
     if (narrow ? n < 8000 : n * d * 4 < 6000000)
         return false;
     return p.nnz_in >= n * std::max<int64_t>(narrow ? 32 : 12, n / 2500);
+}
+
+// Floats of the owned rows of width d in column slices.
+int64_t slice_floats(const digest_partition &p, int32_t d)
+{
+    const int64_t w = digest::kSliceFloats;
+    return p.n_own * ((d + w - 1) / w * w);
 }
 
 void plan_layout(digest_partition &p)
@@ -769,9 +780,9 @@ void plan_layout(digest_partition &p)
     int64_t slices = 0;
     for (int32_t k = 0; k <= p.L; ++k)
         if (sliced_pays(p, p.widths[k]))
-            slices = std::max<int64_t>(slices, ((int64_t)p.n_own + p.n_bnd) *
-                                                   ((p.widths[k] + 31) / 32 * 32));
+            slices = std::max<int64_t>(slices, slice_floats(p, p.widths[k]));
     l.slices = take(sizeof(float) * (size_t)slices);
+    l.slices_floats = slices;
     l.fz = take(sizeof(float) * (size_t)fz);
     l.wt = take(sizeof(float) * (size_t)wt);
     l.tmp = take(sizeof(float) * (size_t)p.n_own * wmax);
@@ -1027,6 +1038,15 @@ bool fuse_forward(const digest_partition &p, int32_t layer, bool transform_first
     return find_tiers(p, Csr::InH, padded_width(d_in)) == nullptr;
 }
 
+// Whether the aggregation of rows of a layer's width d (unpadded) over P_s
+// (InH) or P_in^T (InT) runs out of the L2s: the one place that decides it for
+// the layer calls and their model, so that what runs is what was planned.
+bool use_sliced(const digest_partition &p, Csr which, int32_t d)
+{
+    return (which == Csr::InH || which == Csr::InT) && sliced_pays(p, d) &&
+           !find_tiers(p, which, d) && !find_tiers(p, which, padded_width(d));
+}
+
 // The aggregation over P_s (InH) or P_in^T (InT) out of the XCDs' L2s: the
 // n_own rows of src0 (d floats, row stride ld0; masked by mask > 0, row
 // stride ldm, if given) laid out in column slices, then gathered slice by
@@ -1037,6 +1057,10 @@ digest_status run_sliced(digest_partition *p, Csr which, const float *src0, int3
                          hipStream_t s)
 {
     const bool fwd = which == Csr::InH;
+    const std::vector<SpmmBlock> &blocks = fwd ? p->blocks_s_slice : p->blocks_t_slice;
+    if (blocks.empty() || slice_floats(*p, d) > p->lay.slices_floats)
+        return fail(DIGEST_ESTATE, "layer %d: no sliced aggregation of %d floats was planned",
+                    layer, d);
     float *sl = p->at<float>(p->lay.slices);
     Timed t(p, fwd ? K_SPMM_FWD : K_SPMM_BWD, layer, s);
     if (digest_status st = hip_check(
@@ -1046,8 +1070,7 @@ digest_status run_sliced(digest_partition *p, Csr which, const float *src0, int3
     return hip_check(
         digest::launch_spmm_slice(
             p->at<SpmmBlock>(fwd ? l.blocks_s_slice : l.blocks_t_slice),
-            (int32_t)(fwd ? p->blocks_s_slice : p->blocks_t_slice).size(),
-            fwd ? p->long_s_slice : p->long_t_slice,
+            (int32_t)blocks.size(), fwd ? p->long_s_slice : p->long_t_slice,
             p->at<int32_t>(fwd ? l.s_rowptr : l.t_rowptr),
             p->at<int32_t>(fwd ? l.s_col : l.t_src), p->at<float>(fwd ? l.s_val : l.t_val), sl,
             p->n_own, src1, ld1, d, out, ldo, relu, s),
@@ -1061,10 +1084,6 @@ digest_status run_spmm(digest_partition *p, Csr which, const float *src0, const 
                        bool relu = false, int32_t lds = 0, int32_t out_ld = 0,
                        int32_t out_w = 0)
 {
-    if (which == Csr::InT && !ep && !relu && !out1 && kind < 0 &&
-        !find_tiers(*p, which, d) && sliced_pays(*p, d))
-        return run_sliced(p, which, src0, lds > 0 ? lds : d, nullptr, 0, nullptr, 0,
-                          out_w > 0 ? out_w : d, out, out_ld > 0 ? out_ld : d, false, layer, s);
     const std::vector<SpmmBlock> *blocks = &p->blocks_tf;
     size_t boff = p->lay.blocks_tf;
     int32_t n_long = p->long_tf;
@@ -1115,13 +1134,6 @@ digest_status run_spmm(digest_partition *p, Csr which, const float *src0, const 
                             p->at<int32_t>(o_col), p->at<float>(o_val), src0, src1,
                             n_src0, d, out, s, ep, out1, n_out0, relu, false, lds, out_ld, out_w),
         "spmm");
-}
-
-// An aggregate-first forward whose aggregation runs out of the L2s.
-bool use_sliced(const digest_partition &p, int32_t layer)
-{
-    return sliced_pays(p, p.widths[layer - 1]) && !fuse_forward(p, layer, false) &&
-           !find_tiers(p, Csr::InH, padded_width(p.widths[layer - 1]));
 }
 
 // S = P_b halo_buf[level]: the halo aggregate of level `level` (the halo
@@ -1679,7 +1691,7 @@ digest_status digest_layer_forward(digest_partition *p, int32_t layer, const flo
             if (digest_status st = transform_rows(p, layer, h_in, hs, p->n_bnd, w, T, ldt, s))
                 return st;
         }
-        if (sliced_pays(*p, d_out)) {
+        if (use_sliced(*p, Csr::InH, d_out)) {
             if (digest_status st = run_sliced(p, Csr::InH, T, ldt, nullptr, 0,
                                               T + (int64_t)p->n_own * ldt, ldt, d_out, h_out,
                                               d_out, act == DIGEST_ACT_RELU, layer, s))
@@ -1697,7 +1709,7 @@ digest_status digest_layer_forward(digest_partition *p, int32_t layer, const flo
         float *ah = p->at<float>(p->lay.ah[layer]);
         const int32_t lh = padded_width(d_in);
         const float *src0 = h_in;
-        const bool sliced = use_sliced(*p, layer);
+        const bool sliced = use_sliced(*p, Csr::InH, d_in) && !fuse_forward(*p, layer, false);
         if (lh != d_in && !sliced) {
             float *hp = p->at<float>(p->lay.hpad);
             Timed t(p, K_PAD_ROWS, layer, s);
@@ -1908,8 +1920,9 @@ digest_status backward_transform_first(digest_partition *p, int32_t layer, const
     const bool relu = p->act[layer] == DIGEST_ACT_RELU;
     // An aggregation out of the L2s masks D and pads its rows while laying
     // it out; only the halo rows' aggregation still reads rows of D.
-    const bool sliced = !fused_dh && !dh_halo && sliced_pays(*p, d_out);
-    if (sliced) {
+    const bool sliced = !fused_dh && use_sliced(*p, Csr::InT, d_out);
+    const bool mask_in_slices = sliced && !dh_halo;
+    if (mask_in_slices) {
         if (digest_status st = run_sliced(p, Csr::InT, dh_out, d_out, relu ? h_out : nullptr,
                                           d_out, nullptr, 0, d_out, G, ldg, false, layer, s))
             return st;
@@ -1934,11 +1947,16 @@ digest_status backward_transform_first(digest_partition *p, int32_t layer, const
         src = dp;
         dg = lsrc = ldg;
     }
-    if (!sliced)
+    if (sliced && !mask_in_slices) {
+        if (digest_status st = run_sliced(p, Csr::InT, src, lsrc, nullptr, 0, nullptr, 0, d_out,
+                                          G, ldg, false, layer, s))
+            return st;
+    } else if (!sliced) {
         if (digest_status st = run_spmm(p, Csr::InT, src, nullptr, p->n_own, dg, G, layer, s,
                                         fused_dh ? &ep : nullptr, -1, nullptr, INT32_MAX,
                                         false, lsrc, ldg, dg))
             return st;
+    }
     if (dh_halo) {
         // G_halo = P_out^T D; dh_halo = G_halo W^T (in the same launch when
         // the epilogue applies)
@@ -1956,7 +1974,7 @@ digest_status backward_transform_first(digest_partition *p, int32_t layer, const
         Timed t(p, K_BND_ROWS, layer, s);
         const int32_t *bnd = p->at<int32_t>(p->lay.bnd_local);
         if (digest_status st = hip_check(
-                sliced && relu
+                mask_in_slices && relu
                     ? digest::launch_relu_mask(p->n_bnd, d_out, dh_out, d_out, h_out, d_out, G2,
                                                ldg, s, bnd)
                     : digest::launch_copy_rows(bnd, nullptr, p->n_bnd, dg, src, G2, s, lsrc, ldg),
@@ -2112,17 +2130,22 @@ digest_status layer_backward(digest_partition *p, int32_t layer, const float *h_
                                                       zpre, ldz, wt, d_in, dh_in, d_in, false, s),
                              "fused input gradient");
         }
-        // P_in^T alone, or P_m^T with its halo rows split off
-        const Csr tr = dh_halo ? Csr::FullT : Csr::InT;
-        const int32_t split = dh_halo ? p->n_own : INT32_MAX;
+        // P_in^T alone, or P_m^T with its halo rows split off into halo
+        auto aggregate_t = [&](const float *src, int32_t d, float *out, float *halo) {
+            if (!dh_halo && use_sliced(*p, Csr::InT, d))
+                return run_sliced(p, Csr::InT, src, d, nullptr, 0, nullptr, 0, d, out, d, false,
+                                  layer, s);
+            return run_spmm(p, dh_halo ? Csr::FullT : Csr::InT, src, nullptr, p->n_own, d, out,
+                            layer, s, nullptr, -1, dh_halo ? halo : nullptr,
+                            dh_halo ? p->n_own : INT32_MAX);
+        };
         float *tmp = p->at<float>(p->lay.tmp);
         if (!relu && d_out < d_in) {
             // Narrower output: aggregate D first (width d_out), then times W^T.
             float *gh = p->at<float>(p->lay.tmp_halo);
             if (digest_status st = start_weight_grad())
                 return st;
-            if (digest_status st = run_spmm(p, tr, dh_out, nullptr, p->n_own, d_out, tmp, layer,
-                                            s, nullptr, -1, dh_halo ? gh : nullptr, split))
+            if (digest_status st = aggregate_t(dh_out, d_out, tmp, gh))
                 return st;
             {
                 Timed t(p, K_GEMM_DH, layer, s);
@@ -2158,8 +2181,7 @@ digest_status layer_backward(digest_partition *p, int32_t layer, const float *h_
         }
         if (digest_status st = start_weight_grad())
             return st;
-        return run_spmm(p, tr, tmp, nullptr, p->n_own, d_in, dh_in, layer, s, nullptr, -1,
-                        dh_halo, split);
+        return aggregate_t(tmp, d_in, dh_in, dh_halo);
     }();
     if (sw != s) {
         const digest_status st = join_side(p, s);
@@ -2739,7 +2761,7 @@ digest_status digest_profile_model(const digest_partition *p, int32_t model, dou
                 0.0, p->nnz_in);
             // (a sliced aggregation masks and pads D itself; a ReLU layer's
             // boundary rows are then masked as they are copied)
-            const bool sliced = !pl.dgrad_fused && sliced_pays(*p, p->widths[l]);
+            const bool sliced = !pl.dgrad_fused && use_sliced(*p, Csr::InT, p->widths[l]);
             if (p->n_bnd > 0)
                 put(K_BND_ROWS, l, (sliced && relu ? 12 : 8) * nb * dout + 4 * nb);
             if (sliced)
@@ -2771,7 +2793,8 @@ digest_status digest_profile_model(const digest_partition *p, int32_t model, dou
                 p->nnz_s);
             put(K_GEMM_FWD, l, 4 * (n * di + di * dout + n * dout), 2 * n * di * dout);
         }
-        if (p->widths[l - 1] % 4 && !use_sliced(*p, l))   // the padded copy of h_in
+        if (p->widths[l - 1] % 4 &&   // the padded copy of h_in
+            (pl.forward_fused || !use_sliced(*p, Csr::InH, p->widths[l - 1])))
             put(K_PAD_ROWS, l, 4 * n * (di + padded_width(p->widths[l - 1])));
         put(K_GEMM_DW, l, 4 * (n * di + n * dout * (relu && !pl.backward_fused ? 2 : 1) + di * dout),
             2 * n * di * dout);

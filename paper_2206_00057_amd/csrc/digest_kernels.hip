@@ -3203,9 +3203,8 @@ hipError_t launch_spmm_slice(const SpmmBlock *blocks, int32_t n_blocks, int32_t 
                              const float *src, int32_t n_src, const float *src1, int32_t ld1,
                              int32_t d, float *out, int32_t ldo, bool relu, hipStream_t s)
 {
-    if (n_blocks <= 0 || d <= 0)
-        return hipSuccess;
-    if (n_long < 0 || n_long > n_blocks || ldo < d || n_src < 1 || (src1 && ld1 < d) ||
+    if (n_blocks < 1 || d < 1 ||   // there are rows (n_src >= 1): nothing to do is a mistake
+        n_long < 0 || n_long > n_blocks || ldo < d || n_src < 1 || (src1 && ld1 < d) ||
         (int64_t)n_src * kSliceFloats * 4 > INT32_MAX)   // byte offsets within a slice
         return hipErrorInvalidValue;
     const int64_t per = n_long + ((int64_t)(n_blocks - n_long) + kSpmmWaves - 1) / kSpmmWaves;

@@ -20,6 +20,9 @@ CASES = [
     (12003, 40, (602, 128, 16), 0),     # a ReLU layer transformed first: D masked as it is laid out
     (15001, 12, (101, 101, 64), 0),     # scalar loads, one odd row past the strips
     (16500, 14, (96, 256, 256, 40), 2048),   # above the fused passes' row count
+    # widths below the rule's narrowest that pad to it, no other width sliced
+    (10003, 45, (100, 37), 0),
+    (9001, 45, (100, 128, 39), 0),
 ]
 
 
