@@ -2446,7 +2446,7 @@ __global__ __launch_bounds__(256) void k_gat_softmax(int32_t n_rows,
     float pos = 0.f;
     auto weight = [&](int k, float e) {
         const float w = expf(e - m) * inv;
-        pos += e > 0.f ? w : 0.f;
+        pos += e <= 0.f ? 0.f : w;   // (NaN where e or the row is)
         alpha[k] = e > 0.f ? w : -w;
     };
 #pragma unroll
@@ -2701,7 +2701,7 @@ k_gat_entries(const SpmmBlock *__restrict__ blocks, int32_t n_long, int32_t n_bl
                     ds += ok[u] ? a[u] * (dot - rc[u].w) * (pre > 0.f ? 1.f : g.slope) : 0.f;
                 }
                 const float w = BWD ? a[u] : fabsf(a[u]);
-                const float wp = fmaxf(a[u], 0.f);
+                const float wp = a[u] < 0.f ? 0.f : a[u];   // (a NaN stays one)
 #pragma unroll
                 for (int ch = 0; ch < NCH; ++ch)
 #pragma unroll

@@ -35,3 +35,27 @@ def test_gat_entries(widths, longest):
                     c.layer(2, oracle.IDENTITY, "again")):
         np.testing.assert_array_equal(a.cpu().numpy().view(np.uint32),
                                       b.cpu().numpy().view(np.uint32))
+
+
+@pytest.mark.parametrize("d", [7, 16, 29, 61, 130, 300])
+def test_diverged_attention_reaches_every_gradient(d):
+    """An attention vector with a NaN makes every weight NaN: the row terms,
+    which take LeakyReLU's positive branch of a row, may not lose it."""
+    from paper_2206_00057_amd import digest as D
+    cfg = synth.scaled(synth.CONFIGS["tiny"], 1200, widths=(6, d), classes=d)
+    g = synth.make_graph(cfg, seed=2)
+    part = synth.make_partition(cfg, g, 1)
+    c = Case(g.n, part, (6, d))
+    c.pull(0, synth.relu_normal((g.n, 6), seed=20))
+    n, dev = part.n_own, lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    x, w = synth.relu_normal((n, 6), seed=1), synth.normal((6, d), seed=2)
+    dh, att = synth.normal((n, d), seed=3), synth.normal((d, 2), seed=4)
+    att[d // 2] = np.nan
+    out, dw, datt = (torch.empty(*sh, device="cuda") for sh in ((n, d), (6, d), (d, 2)))
+    dx = torch.empty(n, 6, device="cuda")
+    D.digest_gat_forward(c.h, 1, dev(x), dev(w), dev(att), out, oracle.IDENTITY)
+    # (finite activations, so that the NaN is the weights' alone)
+    D.digest_gat_backward(c.h, 1, dev(x), dev(dh), dev(dh), dev(w), dev(att), dw, datt, dx)
+    ref = c.op.gat_backward(1, x, w, att, dh, dh, oracle.IDENTITY, want_dh_in=True)
+    for got, r, name in zip((dw, datt, dx), ref, ("dw", "datt", "dh_in")):
+        assert np.isnan(r).all() and torch.isnan(got).all(), name
