@@ -1063,15 +1063,20 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Eight floats as the sums of three bf16 each, x = h + m + l: h is x rounded
-// to bf16, m what is left rounded, l what is left then (each step's
-// remainder is exact in fp32, and the three hold all 24 bits of x).
+// Eight floats as the sums of three bf16 each, kSplitScale x = h + m + l: h is
+// x rounded to bf16, m what is left rounded, l what is left then (each step's
+// remainder is exact in fp32).  The scale takes the last bit of the smallest
+// floats (2^-149) to that of the smallest bf16 numbers (2^-133; the matrix
+// cores keep subnormal ones), so that the three hold all 24 bits of every x
+// up to 2^112.  Without it they held 24 bits down to 2^-110 and none below
+// 2^-134.  Of a larger x the parts are NaN.
+constexpr float kSplitScale = 0x1p16f;
 __device__ __forceinline__ void split8(const float (&x)[8], uint4 &h, uint4 &m, uint4 &l)
 {
     uint32_t hu[4], mu[4], lu[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        float a = x[2 * i], b = x[2 * i + 1];
+        float a = x[2 * i] * kSplitScale, b = x[2 * i + 1] * kSplitScale;
         hu[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{a, b}), bf16x2));
         a -= __uint_as_float(hu[i] << 16);
         b -= __uint_as_float(hu[i] & 0xffff0000u);
@@ -1155,7 +1160,8 @@ struct Oct {
 // C = op(A) op(B) in fp32 precision on v_mfma_f32_32x32x16_bf16: every
 // operand element is split into three bf16 (split8) as it is staged in LDS,
 // and of the nine products of the parts the six that reach fp32's last bits
-// are accumulated in fp32 (what is left out is below 2^-26 of a product):
+// are accumulated in fp32 (what is left out is at most about 2^-24 of a
+// product, 2^-28 on average; an fp32 product's own rounding is up to 2^-24):
 // the products of the high parts in one accumulator, the small ones in
 // another, added at the end, so that a sum is rounded once per 16 k (the
 // errors against 64 bits are about a third of the fp32 instructions': 500
@@ -1166,21 +1172,24 @@ struct Oct {
 // sixteen lanes' 16-byte reads fall into different banks).
 // Rows past the operand repeat its last row (their results are not stored).
 // Six bf16 products cost 192 matrix-core cycles where the fp32 instructions
-// need 512 for the same 16 k; splitting costs 5.5 vector operations per
-// staged element, so addresses are a uniform tile base and a fixed offset
-// per lane, and nothing but the last tile of a K range is checked.
-// Measured (fp32 instructions / this): 11,250 x 256 over 500 44 / 33 us,
-// 58,250 x 256 over 602 247 / 148, weight gradients 500 x 256 over 11,250
-// 45 / 36, 602 x 256 over 58,250 243 / 171.  What is left is the chain of
+// need 512 for the same 16 k; splitting costs 6.5 vector operations per
+// staged element, so addresses are a uniform tile base and a fixed offset per
+// lane, and nothing but the last tile of a K range is checked.
+// Measured (fp32 instructions / this): 11,250 x 256 over 500 44.3 / 33.5 us,
+// 58,250 x 256 over 602 216 / 136, its weight gradient beside the D W^T
+// product 381 / 301, 500 x 256 over 11,250 45.0 / 37.0.  The scale's multiply
+// costs 1% of the 64x64 tile's time and 2-4% of the 128x128 tile's (33.5 /
+// 33.2 and 136 / 133 us without it).  What is left is the chain of
 // phases between the barriers: a second LDS buffer with one barrier per tile
 // cost occupancy and was slower (38 and 210 us), and so were three and four
 // tiles in flight.
-// A non-finite operand (or one that rounds past bf16's largest value) makes
-// the split's parts NaN; where an element of C comes out non-finite, its wave
-// sums that 32x32 block again on the fp32 instructions and takes from it the
-// elements that were not finite (no other changes).  Operands that are NaN
-// throughout: 500 x 256 over 11,250 about 146 us where finite ones take 39
-// (summed element by element 4,125), 11,250 x 256 over 500 about 80 more.
+// A non-finite operand (or a finite one past 2^112) makes the split's parts
+// NaN, and a sum past 2^96 is infinite times the scales; where an element of
+// C comes out non-finite, its wave sums that 32x32 block again on the fp32
+// instructions and takes from it the elements that were not finite (no other
+// changes).  Operands that are NaN throughout: 500 x 256 over 11,250 about
+// 146 us where finite ones take 39 (summed element by element 4,125),
+// 11,250 x 256 over 500 about 80 more.
 template <int B_, int DEPTH, bool AT, bool BT, bool AMASK, bool BMASK, bool RELU>
 __global__ __launch_bounds__(256, B_ > 64 ? 2 : 3) void k_gemm(
     int32_t M, int32_t N, int32_t K, int32_t kchunk, const float *__restrict__ A, int32_t lda,
@@ -1370,7 +1379,7 @@ __global__ __launch_bounds__(256, B_ > 64 ? 2 : 3) void k_gemm(
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int r = r0 + (e >> 2) * 8 + (e & 3);
-                float v = acc[i][j][e] + low[i][j][e];
+                float v = (acc[i][j][e] + low[i][j][e]) * (1.f / (kSplitScale * kSplitScale));
                 if (r < M && cn < N) {
                     bad |= (__float_as_uint(v) & 0x7f800000u) == 0x7f800000u ? 1u << e : 0u;
                     if (RELU)

@@ -63,6 +63,26 @@ def test_products_match_float64(n, d_in, d_out):
         assert np.abs(got - ref).max() <= bound, (name, np.abs(got - ref).max(), bound)
 
 
+# binary exponents of h, w and D: each operand in turn as small as a normal
+# float and as a subnormal one (whose parts are below every normal bf16)
+SMALL = [(-118, 40, 40), (40, -118, 40), (40, 40, -118), (-139, 40, 40), (40, -139, 40),
+         (40, 40, -139)]
+
+
+@pytest.mark.parametrize("n,d_in,d_out", [(130, 95, 70), (333, 602, 257), (20001, 101, 130)])
+@pytest.mark.parametrize("exps", SMALL, ids=lambda e: "_".join(map(str, e)))
+def test_small_operands_keep_their_bits(n, d_in, d_out, exps):
+    eh, ew, ed = exps
+    h, w, dh, h_out = inputs(n, d_in, d_out)
+    h, w, dh = np.ldexp(h, eh), np.ldexp(w, ew), np.ldexp(dh, ed)   # (subnormals are rounded)
+    for name, got, ref, e in zip(("forward", "dW", "dH"), products(n, d_in, d_out, h, w, dh, h_out),
+                                 refs(h, w, dh, h_out), (eh + ew, eh + ed, ed + ew)):
+        K = {"forward": d_in, "dW": n, "dH": d_out}[name]
+        # the bound of test_products_match_float64, for products of size 2^e
+        bound = 4 * (4 + np.sqrt(K)) * 2.0 ** -24 * np.sqrt(K) * 2.0 ** e
+        assert np.abs(got - ref).max() <= bound, (name, np.abs(got - ref).max(), bound)
+
+
 @pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, 3.4e38])
 @pytest.mark.parametrize("n,d_in,d_out", [(130, 95, 70), (20001, 101, 130)])
 def test_non_finite_operands_stay_where_they_belong(n, d_in, d_out, bad):
