@@ -683,6 +683,35 @@ bool sliced_pays(const digest_partition &p, int32_t d)
     return p.nnz_in >= n * std::max<int64_t>(narrow ? 32 : 12, n / 2500);
 }
 
+// Whether a GAT layer's pass over the entries at width d gives a wave a strip
+// of rows (kGatStrips), all its lanes to one row's entries at a time, instead
+// of a share of 8 short rows, or a workgroup a row of more than kSpmmLongRow
+// entries.  The lines, by measured layer times (groups / strips, us):
+//   entries per row: a strip needs rows that fill its wave, and saves the
+//     workgroups of medium rows.  Forward, 29,125 rows of 7 floats: mean 50
+//     107 / 94, mean 70 137 / 99, mean 100 195 / 116; 11,250 rows of mean 50
+//     51.6 / 51.9, of 64 floats 81 / 89; 60,000 rows of mean 10 81 / 98.
+//     Backward, by the owned rows of the transpose (a halo row has few
+//     entries): 55 in-partition entries a row 122 / 153, 75 169 / 164, 75 and
+//     hardly any halo 135 / 74; 64 floats: 55 218 / 228, 75 294 / 250.
+//   rows: strips are fewer waves than rows shared by workgroups.  Forward, 7
+//     floats, mean 100: 1,000 rows 23.7 / 23.6, 2,000 29.8 / 26.3; 41 floats:
+//     8,000 rows 86 / 102, 16,000 143 / 151, 29,125 230 / 205.  Backward, 75
+//     entries a row, 41 floats: 8,000 rows 102 / 121, 16,000 169 / 158.
+//   width: wider rows take a wave each anyway (forward, 128 floats: 29,125
+//     rows of mean 100 292 / 349, Flickr-shaped 52 / 92; the backward of 65 to
+//     128 floats would gain on dense rows, 390 / 311, and lose on small
+//     partitions, 69 / 110).
+bool gat_strips(const digest_partition &p, int32_t d, bool backward)
+{
+    const int64_t n = p.n_own;
+    if (d > digest::kGatStripWidth)
+        return false;
+    if (backward)
+        return p.nnz_in >= std::max<int64_t>(64 * n, 1000000);
+    return p.nnz >= 64 * n && n >= (d > 32 ? 20000 : 2000);
+}
+
 // Floats of the owned rows of width d in column slices.
 int64_t slice_floats(const digest_partition &p, int32_t d)
 {
@@ -2496,13 +2525,13 @@ digest_status digest_gat_forward(digest_partition *p, int32_t layer, const float
                     "GAT softmax"))
                 return st;
         }
-        const bool strips = digest::gat_strips(d_out);
+        const bool strips = gat_strips(*p, d_out, false);
         Timed t(p, K_GAT_AGG, layer, s);
         if (digest_status st = hip_check(
                 digest::launch_gat_aggregate(
                     p->at<SpmmBlock>(strips ? p->lay.blocks_f_gat : p->lay.blocks_f),
                     strips ? p->long_f_gat : p->long_f,
-                    (int32_t)(strips ? p->blocks_f_gat : p->blocks_f).size(),
+                    (int32_t)(strips ? p->blocks_f_gat : p->blocks_f).size(), strips,
                     p->at<int32_t>(p->lay.rowptr), p->at<int32_t>(p->lay.col), alpha, Z, d_out,
                     ld, h_out, act == DIGEST_ACT_RELU, p->gat<float>(p->glay.op[layer]), s),
                 "GAT aggregation"))
@@ -2563,16 +2592,15 @@ digest_status digest_gat_backward(digest_partition *p, int32_t layer, const floa
     }
     {
         // dz over every local row, and the source-score gradients (g2[v][0])
-        const bool strips = digest::gat_strips(d_out);
+        const bool strips = gat_strips(*p, d_out, true);
         Timed t(p, K_GAT_ENTRIES, layer, s);
         if (digest_status st = hip_check(
                 digest::launch_gat_backward(
                     p->at<SpmmBlock>(strips ? p->lay.blocks_tf_gat : p->lay.blocks_tf),
                     strips ? p->long_tf_gat : p->long_tf,
-                    (int32_t)(strips ? p->blocks_tf_gat : p->blocks_tf).size(),
-                    p->at<int32_t>(p->lay.t_rowptr),
-                    p->at<int32_t>(p->lay.t_src), S, Z, dO, att, d_out, ld, slope, p->n_own,
-                    g2, dz, s),
+                    (int32_t)(strips ? p->blocks_tf_gat : p->blocks_tf).size(), strips,
+                    p->at<int32_t>(p->lay.t_rowptr), p->at<int32_t>(p->lay.t_src), S, Z, dO,
+                    att, d_out, ld, slope, p->n_own, g2, dz, s),
                 "GAT entry gradient"))
             return st;
     }

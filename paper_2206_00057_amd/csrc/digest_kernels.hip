@@ -2398,7 +2398,7 @@ __device__ __forceinline__ float leaky(float x, float slope) { return x > 0.f ? 
 // LeakyReLU(s[i][1] + s[col[k]][0]), s [rows][2] (source, target score),
 // with the sign bit set where the score sum is not positive (the other
 // branch of LeakyReLU); stat[i] = {the row's maximum, 1 / the sum of
-// exponentials, the sum of the positive branch's weights, 0}, zeros for an
+// exponentials, the positive branch's share of the sum, 0}, zeros for an
 // empty row: with it the backward forms a weight again from the scores.
 // A wave takes a row and strides over its entries three times (the
 // maximum, the sum of exponentials, the weights), combining its lanes by a
@@ -2457,34 +2457,38 @@ __global__ __launch_bounds__(256) void k_gat_softmax(int32_t n_rows,
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1)
         m = fmaxf(m, __shfl_xor(m, off));
-    float l = 0.f;
+    // an entry's exponential, negative where its score sum is not positive
+    // (where the score is not: slope >= 0)
+    auto signed_exp = [&](float e) { return e > 0.f ? expf(e - m) : -expf(e - m); };
+    float l = 0.f, pos = 0.f;
+    auto add = [&](float x) {
+        l += fabsf(x);
+        pos += x < 0.f ? 0.f : x;   // (a NaN stays one)
+    };
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-        l += kb + lane + u * kWave < ke ? expf(ec[u] - m) : 0.f;
+    for (int u = 0; u < U; ++u) {
+        ec[u] = kb + lane + u * kWave < ke ? signed_exp(ec[u]) : 0.f;
+        add(ec[u]);
+    }
     for (int k0 = kb + SPAN; k0 < ke; k0 += SPAN) {
         float e[U];
         scores(k0, e);
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            l += k0 + lane + u * kWave < ke ? expf(e[u] - m) : 0.f;
+            add(k0 + lane + u * kWave < ke ? signed_exp(e[u]) : 0.f);
     }
 #pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1)
+    for (int off = kWave / 2; off > 0; off >>= 1) {
         l += __shfl_xor(l, off);
+        pos += __shfl_xor(pos, off);
+    }
     const float inv = 1.f / l;
-    // e > 0 exactly where the score sum is positive (slope >= 0; at slope 0
-    // the other branch's scores are zeros)
-    float pos = 0.f;
-    auto weight = [&](int k, float e) {
-        const float w = expf(e - m) * inv;
-        pos += e <= 0.f ? 0.f : w;   // (NaN where e or the row is)
-        alpha[k] = e > 0.f ? w : -w;
-    };
+    pos *= inv;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int k = kb + lane + u * kWave;
         if (k < ke)
-            weight(k, ec[u]);
+            alpha[k] = ec[u] * inv;
     }
     for (int k0 = kb + SPAN; k0 < ke; k0 += SPAN) {
         float e[U];
@@ -2493,12 +2497,9 @@ __global__ __launch_bounds__(256) void k_gat_softmax(int32_t n_rows,
         for (int u = 0; u < U; ++u) {
             const int k = k0 + lane + u * kWave;
             if (k < ke)
-                weight(k, e[u]);
+                alpha[k] = signed_exp(e[u]) * inv;
         }
     }
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1)
-        pos += __shfl_xor(pos, off);
     if (lane == 0)
         stat[row] = make_float4(m, inv, pos, 0.f);
 }
@@ -2553,18 +2554,19 @@ __global__ __launch_bounds__(256) void k_gat_rows(int32_t n, int32_t d, int32_t 
     }
 }
 
-// Sum of x over the caller's group of GL lanes (4 .. 64), in every lane.
+// Sum of x over the caller's group of GL lanes (2 .. 64), in every lane.
 template <int GL>
 __device__ __forceinline__ float group_sum(float x)
 {
-    static_assert(GL == 4 || GL == 8 || GL == 16 || GL == 32 || GL == 64, "lane groups");
+    static_assert(GL == 2 || GL == 4 || GL == 8 || GL == 16 || GL == 32 || GL == 64, "lane groups");
     auto dpp = [](float v, auto ctrl) {
         return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v),
                                                           decltype(ctrl)::value, 0xF, 0xF,
                                                           false));
     };
     x += dpp(x, std::integral_constant<int, 0xB1>{});    // quad_perm [1, 0, 3, 2]
-    x += dpp(x, std::integral_constant<int, 0x4E>{});    // quad_perm [2, 3, 0, 1]
+    if constexpr (GL >= 4)
+        x += dpp(x, std::integral_constant<int, 0x4E>{});    // quad_perm [2, 3, 0, 1]
     if constexpr (GL >= 8)
         x += dpp(x, std::integral_constant<int, 0x141>{});   // row_half_mirror
     if constexpr (GL >= 16)
@@ -2623,15 +2625,20 @@ struct GatEntries {
 // A lane group of GL lanes holds a row as NCH float4 each and has U entries
 // in flight.  The n_long first blocks are rows whose entries a whole
 // workgroup splits, its waves' sums added in LDS in wave order.  The others,
-// by MODE: kGatGroups, a short-row block (at most 8 rows) per wave, a lane
-// group taking each row (rows of at most 32 floats, where a wave per row
-// would leave most lanes idle: 43,018 rows of mean 21, 4 floats, 183 us);
-// kGatStrips, a strip of consecutive rows per wave (as in k_spmm_slice), its
-// groups splitting a row's entries; kGatWaves, the rows of one workgroup, one
-// per wave.  All sums have a fixed order.
+// by MODE: kGatGroups, a short-row block (at most 8 rows) dealt to as many
+// waves as it takes with SUB lane groups to a row, which split its entries
+// (one group to a row leaves half a wave's lanes idle and walks a row of tens
+// of entries in as many dependent steps: Flickr-shaped layer of 7 floats,
+// forward 33.8 -> 29.8 us and backward 39.5 -> 31.6, of 64 floats 56.2 -> 47.5
+// and 73.5 -> 59.0 with a wave per strip before); kGatStrips, a strip of
+// consecutive rows per wave (as in k_spmm_slice), all its groups splitting a
+// row's entries; kGatWaves, the rows of one workgroup, one per wave.  A narrow
+// row that a workgroup shares is split into steps of 64 entries a wave (steps
+// of 128 left half the loads of a row of 500 entries unused: Reddit-shaped
+// backward of 7 floats 543 -> 291 us).  All sums have a fixed order.
 enum GatMode { kGatGroups, kGatStrips, kGatWaves };
 
-template <int GL, int NCH, int U, bool BWD, int MODE>
+template <int GL, int NCH, int U, bool BWD, int MODE, int SUB>
 __global__ __launch_bounds__(kSpmmThreads) void
 k_gat_entries(const SpmmBlock *__restrict__ blocks, int32_t n_long, int32_t n_blocks,
               const GatEntries g)
@@ -2648,18 +2655,20 @@ k_gat_entries(const SpmmBlock *__restrict__ blocks, int32_t n_long, int32_t n_bl
 
     // this workgroup's block: one row for all waves, or this wave's rows
     const bool long_row = wb < n_long;   // uniform
-    const int32_t bi = long_row || MODE == kGatWaves
-                           ? wb
-                           : n_long + (wb - n_long) * kSpmmWaves + wave;
+    constexpr int PARTS = MODE == kGatGroups ? GL * SUB * 8 / kWave : 1;   // waves a block
+    static_assert(MODE != kGatGroups || (PARTS >= 1 && kSpmmWaves % PARTS == 0), "rows of a wave");
+    const int32_t wi = (wb - n_long) * kSpmmWaves + wave;
+    const int32_t bi = long_row || MODE == kGatWaves ? wb : n_long + wi / PARTS;
     if (bi >= n_blocks)
         return;
     const SpmmBlock b = blocks[bi];
-    const bool own = MODE == kGatGroups && !long_row;   // a group has its own row
+    const bool own = MODE == kGatGroups && !long_row;   // SUB groups have their own row
     int32_t r = b.row, rend = b.row + (long_row ? 1 : b.nrows);
     if (!long_row && MODE != kGatStrips) {
-        const int32_t first = MODE == kGatWaves ? wave : grp;
+        const int32_t first =
+            MODE == kGatWaves ? wave : wi % PARTS * (G / SUB) + grp / SUB;
         if (first >= b.nrows)
-            return;   // a whole wave, or whole groups (which share nothing)
+            return;   // a whole wave, or whole rows' groups (which share nothing)
         r += first;
         rend = r + 1;
     }
@@ -2691,61 +2700,74 @@ k_gat_entries(const SpmmBlock *__restrict__ blocks, int32_t n_long, int32_t n_bl
                     acc[a][ch][v] = 0.f;
             }
         }
-        for (int32_t k0 = kb; k0 < ke; k0 += own ? U : U * G) {
-            int32_t i[U];
-            bool ok[U];
-            float a[U];
+        // UE entries in flight per lane group, the entries dealt to `of` groups
+        auto sum_entries = [&](auto ue, auto of, int32_t mine) {
+            constexpr int UE = decltype(ue)::value, OF = decltype(of)::value;
+            for (int32_t k0 = kb; k0 < ke; k0 += UE * OF) {
+                int32_t i[UE];
+                bool ok[UE];
+                float a[UE];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int32_t k = k0 + (own ? u : u * G + grp);
-                ok[u] = k < ke;
-                const int32_t kc = ok[u] ? k : ke - 1;
-                i[u] = g.col[kc];
-                if constexpr (!BWD)
-                    a[u] = ok[u] ? g.alpha[kc] : 0.f;
-            }
-            float4 rc[U];
-            float x[U][NCH][4];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if constexpr (BWD)
-                    rc[u] = *reinterpret_cast<const float4 *>(g.src + (int64_t)i[u] * g.lds +
-                                                              g.ld);
-#pragma unroll
-                for (int ch = 0; ch < NCH; ++ch) {
-                    const int cv = ch * GL + gl;   // past the width: vector 0 again, not used
-                    load_vec<4>(g.src + (int64_t)i[u] * g.lds + (cv < dv ? cv : 0) * 4, x[u][ch]);
+                for (int u = 0; u < UE; ++u) {
+                    const int32_t k = k0 + u * OF + mine;
+                    ok[u] = k < ke;
+                    const int32_t kc = ok[u] ? k : ke - 1;
+                    i[u] = g.col[kc];
+                    if constexpr (!BWD)
+                        a[u] = ok[u] ? g.alpha[kc] : 0.f;
                 }
-            }
+                float4 rc[UE];
+                float x[UE][NCH][4];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if constexpr (BWD) {
-                    float dot = 0.f;   // z is zero past the width
+                for (int u = 0; u < UE; ++u) {
+                    if constexpr (BWD)
+                        rc[u] = *reinterpret_cast<const float4 *>(g.src + (int64_t)i[u] * g.lds +
+                                                                  g.ld);
+#pragma unroll
+                    for (int ch = 0; ch < NCH; ++ch) {
+                        const int cv = ch * GL + gl;   // past the width: vector 0 again, not used
+                        load_vec<4>(g.src + (int64_t)i[u] * g.lds + (cv < dv ? cv : 0) * 4, x[u][ch]);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < UE; ++u) {
+                    if constexpr (BWD) {
+                        // (all of rec is loaded here: a part of it that only an entry
+                        // in the row uses would be loaded, and waited for, behind ok)
+                        asm("" : "+v"(rc[u].x), "+v"(rc[u].y), "+v"(rc[u].z), "+v"(rc[u].w));
+                        float dot = 0.f;   // z is zero past the width
+#pragma unroll
+                        for (int ch = 0; ch < NCH; ++ch)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v)
+                                dot = fmaf(z[ch][v], x[u][ch][v], dot);
+                        dot = group_sum<GL>(dot);
+                        const float pre = rc[u].x + sv;
+                        a[u] = ok[u] ? expf(leaky(pre, g.slope) - rc[u].y) * rc[u].z : 0.f;
+                        ds += ok[u] ? a[u] * (dot - rc[u].w) * (pre > 0.f ? 1.f : g.slope) : 0.f;
+                    }
+                    const float w = BWD ? a[u] : fabsf(a[u]);
+                    const float wp = a[u] < 0.f ? 0.f : a[u];   // (a NaN stays one)
 #pragma unroll
                     for (int ch = 0; ch < NCH; ++ch)
 #pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            dot = fmaf(z[ch][v], x[u][ch][v], dot);
-                    dot = group_sum<GL>(dot);
-                    const float pre = rc[u].x + sv;
-                    a[u] = ok[u] ? expf(leaky(pre, g.slope) - rc[u].y) * rc[u].z : 0.f;
-                    ds += ok[u] ? a[u] * (dot - rc[u].w) * (pre > 0.f ? 1.f : g.slope) : 0.f;
+                        for (int v = 0; v < 4; ++v) {
+                            acc[0][ch][v] = fmaf(w, x[u][ch][v], acc[0][ch][v]);
+                            if constexpr (!BWD)
+                                acc[ACC - 1][ch][v] = fmaf(wp, x[u][ch][v], acc[ACC - 1][ch][v]);
+                        }
                 }
-                const float w = BWD ? a[u] : fabsf(a[u]);
-                const float wp = a[u] < 0.f ? 0.f : a[u];   // (a NaN stays one)
-#pragma unroll
-                for (int ch = 0; ch < NCH; ++ch)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        acc[0][ch][v] = fmaf(w, x[u][ch][v], acc[0][ch][v]);
-                        if constexpr (!BWD)
-                            acc[ACC - 1][ch][v] = fmaf(wp, x[u][ch][v], acc[ACC - 1][ch][v]);
-                    }
             }
-        }
-        if (!own) {
+        };
+        if (own)
+            sum_entries(std::integral_constant<int, U>{}, std::integral_constant<int, SUB>{},
+                        grp % SUB);
+        else
+            sum_entries(std::integral_constant<int, MODE == kGatGroups ? (U < GL ? U : GL) : U>{},
+                        std::integral_constant<int, G>{}, grp);
 #pragma unroll
-            for (int off = GL; off < kWave; off <<= 1) {
+        for (int off = GL; off < kWave; off <<= 1) {   // uniform
+            if (off < GL * SUB || !own) {
 #pragma unroll
                 for (int c = 0; c < ACC; ++c)
 #pragma unroll
@@ -2791,7 +2813,7 @@ k_gat_entries(const SpmmBlock *__restrict__ blocks, int32_t n_long, int32_t n_bl
                     }
                 ds += red[w][ACC * W];
             }
-        } else if (!own && grp != 0) {
+        } else if (own ? grp % SUB != 0 : grp != 0) {
             continue;
         }
         // one group stores the row; loads are unconditional, so that they
@@ -3723,8 +3745,6 @@ hipError_t launch_fill_zero(float *p, int64_t count, hipStream_t s)
     return hipGetLastError();
 }
 
-bool gat_strips(int32_t d) { return d > 32 && d <= 64; }
-
 hipError_t launch_gat_softmax(int32_t n_rows, const int32_t *rowptr, const int32_t *col,
                               const float *s, float slope, float *alpha, float *stat,
                               hipStream_t st)
@@ -3753,21 +3773,23 @@ hipError_t launch_gat_rows(int32_t n, int32_t d, int32_t ld, const float *s, con
 
 namespace {
 
-template <int GL, int NCH, int U, bool BWD, int MODE>
+template <int GL, int NCH, int U, bool BWD, int MODE, int SUB = 1>
 hipError_t gat_entries_t(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks,
                          const GatEntries &g, hipStream_t st)
 {
-    // a workgroup's waves take a block each, or share one
+    // a workgroup's waves share a block, or take one (or its part of one) each
+    const int parts = MODE == kGatGroups ? GL * SUB * 8 / kWave : 1;
     const int64_t grid =
-        MODE == kGatWaves ? n_blocks
-                          : n_long + ((int64_t)(n_blocks - n_long) + kSpmmWaves - 1) / kSpmmWaves;
-    hipLaunchKernelGGL((k_gat_entries<GL, NCH, U, BWD, MODE>), dim3((unsigned)grid),
+        MODE == kGatWaves
+            ? n_blocks
+            : n_long + ((int64_t)(n_blocks - n_long) * parts + kSpmmWaves - 1) / kSpmmWaves;
+    hipLaunchKernelGGL((k_gat_entries<GL, NCH, U, BWD, MODE, SUB>), dim3((unsigned)grid),
                        dim3(kSpmmThreads), 0, st, blocks, n_long, n_blocks, g);
     return hipGetLastError();
 }
 
 template <bool BWD>
-hipError_t gat_entries(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks,
+hipError_t gat_entries(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks, bool strips,
                        const GatEntries &g, hipStream_t st)
 {
     if (n_blocks <= 0)
@@ -3776,14 +3798,28 @@ hipError_t gat_entries(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks
         n_long > n_blocks)
         return hipErrorInvalidValue;
     const int dv = g.ld / 4;
+#define DIGEST_GAT(...) return gat_entries_t<__VA_ARGS__>(blocks, n_long, n_blocks, g, st)
+    if (strips) {   // rows of at most kGatStripWidth floats
+        if (dv <= 2)
+            DIGEST_GAT(2, 1, 2, BWD, kGatStrips);
+        if (dv <= 4)
+            DIGEST_GAT(4, 1, BWD ? 2 : 4, BWD, kGatStrips);
+        if (dv <= 8)
+            DIGEST_GAT(8, 1, BWD ? 2 : 8, BWD, kGatStrips);
+        if (dv <= 16)
+            DIGEST_GAT(16, 1, BWD ? 4 : 8, BWD, kGatStrips);
+        return hipErrorInvalidValue;
+    }
+    if (dv <= 2)
+        DIGEST_GAT(2, 1, 4, BWD, kGatGroups, 4);
     if (dv <= 4)
-        return gat_entries_t<4, 1, 8, BWD, kGatGroups>(blocks, n_long, n_blocks, g, st);
+        DIGEST_GAT(4, 1, 4, BWD, kGatGroups, BWD ? 2 : 4);
     if (dv <= 8)
-        return gat_entries_t<8, 1, 8, BWD, kGatGroups>(blocks, n_long, n_blocks, g, st);
-    if (gat_strips(g.d))
-        return gat_entries_t<8, 2, BWD ? 3 : 4, BWD, kGatStrips>(blocks, n_long, n_blocks, g, st);
+        DIGEST_GAT(8, 1, 4, BWD, kGatGroups, BWD ? 2 : 4);
+    if (dv <= 16)
+        DIGEST_GAT(16, 1, 4, BWD, kGatGroups, BWD ? 1 : 2);
     if (dv <= 32)
-        return gat_entries_t<32, 1, 4, BWD, kGatWaves>(blocks, n_long, n_blocks, g, st);
+        DIGEST_GAT(32, 1, 4, BWD, kGatWaves);
     // The backward takes whole waves per entry: fewer registers a lane, so
     // more waves (Flickr-shaped, 256 floats: 38 us, groups of 32 lanes 52, of
     // 16 97; 100,000 rows of mean 36: 758, 1,008); the forward, with two
@@ -3791,35 +3827,36 @@ hipError_t gat_entries(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks
     // 12: 117, whole waves 156).
     constexpr int GL = BWD ? 64 : 32;
     if (dv <= 64)
-        return gat_entries_t<GL, 64 / GL, 4, BWD, kGatWaves>(blocks, n_long, n_blocks, g, st);
-    return gat_entries_t<GL, 128 / GL, 2, BWD, kGatWaves>(blocks, n_long, n_blocks, g, st);
+        DIGEST_GAT(GL, 64 / GL, 4, BWD, kGatWaves);
+    DIGEST_GAT(GL, 128 / GL, 2, BWD, kGatWaves);
+#undef DIGEST_GAT
 }
 
 }  // namespace
 
 hipError_t launch_gat_aggregate(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks,
-                                const int32_t *rowptr, const int32_t *col, const float *alpha,
-                                const float *z, int32_t d, int32_t ld, float *out, bool relu,
+                                bool strips, const int32_t *rowptr, const int32_t *col,
+                                const float *alpha, const float *z, int32_t d, int32_t ld, float *out, bool relu,
                                 float *op, hipStream_t st)
 {
     GatEntries g{};
     g.rowptr = rowptr, g.col = col, g.src = z, g.lds = ld, g.ld = ld, g.d = d;
     g.alpha = alpha, g.out = out, g.relu = relu, g.op = op;
     g.vout = d % 4 == 0 && ((uintptr_t)out % 16) == 0;
-    return gat_entries<false>(blocks, n_long, n_blocks, g, st);
+    return gat_entries<false>(blocks, n_long, n_blocks, strips, g, st);
 }
 
 hipError_t launch_gat_backward(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks,
-                               const int32_t *rowptr, const int32_t *col, const float *s,
-                               const float *z, const float *dO, const float *att,
-                               int32_t d, int32_t ld, float slope, int32_t n_own, float *g2,
+                               bool strips, const int32_t *rowptr, const int32_t *col,
+                               const float *s, const float *z, const float *dO,
+                               const float *att, int32_t d, int32_t ld, float slope, int32_t n_own, float *g2,
                                float *dz, hipStream_t st)
 {
     GatEntries g{};
     g.rowptr = rowptr, g.col = col, g.src = dO, g.lds = ld + 4, g.ld = ld, g.d = d;
     g.s = s, g.z = z, g.att = att;
     g.slope = slope, g.n_own = n_own, g.g2 = g2, g.dz = dz;
-    return gat_entries<true>(blocks, n_long, n_blocks, g, st);
+    return gat_entries<true>(blocks, n_long, n_blocks, strips, g, st);
 }
 
 }  // namespace digest

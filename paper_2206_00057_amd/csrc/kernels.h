@@ -232,18 +232,18 @@ hipError_t launch_fill_zero(float *p, int64_t count, hipStream_t s);
 // set where LeakyReLU takes its other branch; stat is four floats per owned
 // row, 16-byte aligned; rows of z, op and dz are ld floats apart (d rounded
 // up to 4, 16-byte aligned).  The blocks list the n_long long-row blocks
-// first, then strips of rows for one wave where gat_strips(d), else runs of
-// at most 8 rows.
+// first, then with `strips` (d <= kGatStripWidth) strips of rows for one wave,
+// else runs of at most 8 rows.
 constexpr int kGatMaxWidth = 512;
-bool gat_strips(int32_t d);
+constexpr int kGatStripWidth = 64;
 // |alpha[k]| = softmax over row i's entries of LeakyReLU(s[i][1] + s[col k][0]).
 hipError_t launch_gat_softmax(int32_t n_rows, const int32_t *rowptr, const int32_t *col,
                               const float *s, float slope, float *alpha, float *stat,
                               hipStream_t st);
 // out = act(sum |alpha| z) [rows][d]; op: the part with positive alpha.
 hipError_t launch_gat_aggregate(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks,
-                                const int32_t *rowptr, const int32_t *col, const float *alpha,
-                                const float *z, int32_t d, int32_t ld, float *out, bool relu,
+                                bool strips, const int32_t *rowptr, const int32_t *col,
+                                const float *alpha, const float *z, int32_t d, int32_t ld, float *out, bool relu,
                                 float *op, hipStream_t st);
 // The backward's row terms: dO = dh_out (masked by h_out > 0 with relu; its
 // rows are ld + 4 floats apart, the last four for the entries), and g2[i][1]
@@ -254,9 +254,9 @@ hipError_t launch_gat_rows(int32_t n, int32_t d, int32_t ld, const float *s, con
 // dz over the rows v of P_m^T (all local rows), with the score terms, and
 // g2[v][0] = v's sum of score gradients, g2[v][1] = 0 for v >= n_own.
 hipError_t launch_gat_backward(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks,
-                               const int32_t *rowptr, const int32_t *col, const float *s,
-                               const float *z, const float *dO, const float *att,
-                               int32_t d, int32_t ld, float slope, int32_t n_own, float *g2,
+                               bool strips, const int32_t *rowptr, const int32_t *col,
+                               const float *s, const float *z, const float *dO,
+                               const float *att, int32_t d, int32_t ld, float slope, int32_t n_own, float *g2,
                                float *dz, hipStream_t st);
 
 // GEMM K step; the smallest workgroup tile of C is kGemmBM x kGemmBN.

@@ -235,16 +235,15 @@ hipError_t launch_fill_zero(float *p, int64_t n, hipStream_t)
     std::memset(p, 0, sizeof(float) * n);
     return hipSuccess;
 }
-bool gat_strips(int32_t) { return false; }
 hipError_t launch_gat_softmax(int32_t, const int32_t *, const int32_t *, const float *, float,
                               float *, float *, hipStream_t) { return kNo; }
-hipError_t launch_gat_aggregate(const SpmmBlock *, int32_t, int32_t, const int32_t *,
+hipError_t launch_gat_aggregate(const SpmmBlock *, int32_t, int32_t, bool, const int32_t *,
                                 const int32_t *, const float *, const float *, int32_t, int32_t,
                                 float *, bool, float *, hipStream_t) { return kNo; }
 hipError_t launch_gat_rows(int32_t, int32_t, int32_t, const float *, const float *, const float *,
                            const float *, const float *, bool, float, float *, float *,
                            hipStream_t) { return kNo; }
-hipError_t launch_gat_backward(const SpmmBlock *, int32_t, int32_t, const int32_t *,
+hipError_t launch_gat_backward(const SpmmBlock *, int32_t, int32_t, bool, const int32_t *,
                                const int32_t *, const float *, const float *, const float *,
                                const float *, int32_t, int32_t, float, int32_t, float *, float *,
                                hipStream_t) { return kNo; }

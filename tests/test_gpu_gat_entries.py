@@ -1,12 +1,14 @@
 """The GAT layer's passes over the entries at every width class, with a row
 of more entries than one wave takes, repeated entries, rows without halo
 columns, and every workspace byte set before the first write."""
+import dataclasses
+
 import numpy as np
 import pytest
 
 import oracle
 from paper_2206_00057_amd import synth
-from test_gpu_gat import Case, _need_gpu  # noqa: F401  (fixture)
+from test_gpu_gat import X_BITS, Case, _need_gpu, dyadic  # noqa: F401  (fixture)
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -35,6 +37,27 @@ def test_gat_entries(widths, longest):
                     c.layer(2, oracle.IDENTITY, "again")):
         np.testing.assert_array_equal(a.cpu().numpy().view(np.uint32),
                                       b.cpu().numpy().view(np.uint32))
+
+
+@pytest.mark.parametrize("longest", [0, 2500])
+def test_gat_strips(longest):
+    """Rows dense enough for a wave each, at every width that takes strips."""
+    widths = (3, 5, 16, 29, 64)
+    cfg = dataclasses.replace(synth.CONFIGS["dense"], name="strips", n=41000, blocks=2,
+                              c=55 / 490.0, cap=2000, p_intra=0.85, widths=widths,
+                              classes=widths[-1])
+    g = synth.make_graph(cfg)
+    part = synth.scramble_rows(synth.make_partition(cfg, g, 1), seed=5, long_row=longest)
+    c = Case(g.n, part, widths, seed=2)
+    assert part.n_own > 20000 and c.h.nnz_in > 64 * part.n_own
+    c.ws.fill_(255)
+    c.D.digest_partition_bind_workspace(c.h, c.ws)
+    c.gws.fill_(255)
+    c.D.digest_gat_bind_workspace(c.h, c.gws)
+    for layer in (1, 2, 3, 4):
+        c.pull(layer - 1, dyadic(synth.relu_normal((g.n, widths[layer - 1]), seed=20 + layer),
+                                 X_BITS))
+        c.layer(layer, oracle.RELU if layer % 2 else oracle.IDENTITY, f"layer {layer}", grid=True)
 
 
 @pytest.mark.parametrize("d", [7, 16, 29, 61, 130, 300])
