@@ -323,12 +323,14 @@ digest_status digest_pull_add(digest_partition *p, int32_t level, float *gstore,
  * GCN calls are unaffected by it.
  */
 
-/* Bytes of the GAT workspace (256-byte aligned device memory). */
+/* Bytes of the GAT workspace (256-byte aligned device memory).  Errors:
+ * DIGEST_EINVAL, DIGEST_ENOMEM (host memory for the GAT layout). */
 digest_status digest_gat_query(const digest_partition *p, size_t *workspace_bytes);
 
 /* Bind the GAT workspace (caller-owned device memory, at least the queried
- * size, 256-byte aligned).  Nothing is uploaded.  Errors: DIGEST_EINVAL,
- * DIGEST_ENOMEM (too small). */
+ * size, 256-byte aligned); uploads the work lists of dense partitions on the
+ * stream.  Errors: DIGEST_EINVAL, DIGEST_ENOMEM (too small, or host memory),
+ * DIGEST_EHIP. */
 digest_status digest_gat_bind_workspace(digest_partition *p, void *dev_ptr, size_t bytes,
                                         void *hip_stream);
 

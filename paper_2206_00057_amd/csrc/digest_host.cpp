@@ -11,6 +11,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <numeric>
 #include <string>
@@ -465,7 +466,8 @@ struct digest_partition {
     // sliced_pays says no)
     std::vector<SpmmBlock> blocks_s_slice, blocks_t_slice;
     int32_t long_s_slice = 0, long_t_slice = 0;
-    // P_m and P_m^T for the GAT layer's passes
+    // P_m and P_m^T in strips for the GAT layer's passes (empty where
+    // gat_strips says no to every width), built with the GAT layout
     std::vector<SpmmBlock> blocks_f_gat, blocks_tf_gat;
     int32_t long_f_gat = 0, long_tf_gat = 0;
     // DIGEST_PULL_ROWS: a pull fills the halo buffer, then S from it;
@@ -492,7 +494,6 @@ struct digest_partition {
         size_t blocks_f, blocks_t, blocks_tf, blocks_th;
         size_t s_rowptr, s_col, s_val, b_rowptr, b_col, b_gcol, b_val, blocks_s, blocks_b;
         size_t blocks_s_rows, blocks_t_rows, blocks_s_slice, blocks_t_slice;
-        size_t blocks_f_gat, blocks_tf_gat;
         size_t slices;                  // a sliced aggregation's source in column slices
         int64_t slices_floats;          // (its size)
         size_t fuse_order, fuse_order_t;   // per owned row, uint8 (see fuse_order below)
@@ -516,10 +517,12 @@ struct digest_partition {
 
     // GAT state, in a workspace of its own (digest_gat_bind_workspace)
     struct GatLayout {
+        size_t blocks_f, blocks_tf;        // the strips
         std::vector<size_t> z, s, stat, op;   // per layer 1..L (index 0 unused)
         size_t alpha, d_o, dz, g2, part;
         size_t total;
     } glay{};
+    std::once_flag gat_planned;
     char *gws = nullptr;
     std::vector<char> gat_done;      // per layer: a GAT forward since the GAT bind
     std::vector<int64_t> gat_gen;    // per layer: pull_gen of level layer-1 at that forward
@@ -756,8 +759,6 @@ void plan_layout(digest_partition &p)
     l.blocks_t_rows = take(sizeof(SpmmBlock) * p.blocks_t_rows.size());
     l.blocks_s_slice = take(sizeof(SpmmBlock) * p.blocks_s_slice.size());
     l.blocks_t_slice = take(sizeof(SpmmBlock) * p.blocks_t_slice.size());
-    l.blocks_f_gat = take(sizeof(SpmmBlock) * p.blocks_f_gat.size());
-    l.blocks_tf_gat = take(sizeof(SpmmBlock) * p.blocks_tf_gat.size());
     l.blocks_b = take(sizeof(SpmmBlock) * p.blocks_b.size());
     l.halo_buf.assign(p.L, 0);
     l.hagg.assign(p.L, 0);
@@ -828,7 +829,10 @@ void plan_layout(digest_partition &p)
     l.total = o;
 }
 
-// The GAT workspace: per layer the transformed rows z, their scores, the
+// The GAT layer's strips and its workspace's layout, on the first GAT call: a
+// partition of GCN layers does not pay for them (building the strips took a
+// quarter of a Flickr-shaped partition's creation).
+// The workspace: the strips, per layer the transformed rows z, their scores, the
 // softmax statistics and the positive branch's part of the output (kept from
 // the forward for the backward), and scratch sized for the widest layer.
 // Rows are padded to whole 16-byte vectors.
@@ -842,6 +846,19 @@ void plan_gat_layout(digest_partition &p)
         return r;
     };
     const int64_t R = (int64_t)p.n_own + p.n_halo;
+    bool strips = false, strips_t = false;
+    for (int32_t k = 1; k <= p.L; ++k) {
+        strips = strips || gat_strips(p, p.widths[k], false);
+        strips_t = strips_t || gat_strips(p, p.widths[k], true);
+    }
+    if (strips)
+        p.long_f_gat = build_slice_blocks(p.rowptr.data(), p.n_own, p.blocks_f_gat, kGatStrips,
+                                          kGatMinWork, kGatLong);
+    if (strips_t)
+        p.long_tf_gat = build_slice_blocks(p.t_rowptr.data(), (int32_t)R, p.blocks_tf_gat,
+                                           kGatStrips, kGatMinWork, kGatLong);
+    l.blocks_f = take(sizeof(SpmmBlock) * p.blocks_f_gat.size());
+    l.blocks_tf = take(sizeof(SpmmBlock) * p.blocks_tf_gat.size());
     l.z.assign(p.L + 1, 0);
     l.s.assign(p.L + 1, 0);
     l.stat.assign(p.L + 1, 0);
@@ -867,6 +884,18 @@ void plan_gat_layout(digest_partition &p)
     l.g2 = take(sizeof(float) * (size_t)(R * 2));
     l.part = take(sizeof(float) * (size_t)part);
     l.total = o;
+}
+
+digest_status plan_gat(const digest_partition *cp)
+{
+    // (what is cached depends on the partition alone; any thread may ask first)
+    digest_partition *p = const_cast<digest_partition *>(cp);
+    try {
+        std::call_once(p->gat_planned, [&]() { plan_gat_layout(*p); });
+    } catch (const std::bad_alloc &) {
+        return fail(DIGEST_ENOMEM, "host memory for the GAT layout");
+    }
+    return DIGEST_OK;
 }
 
 // RAII bracket of one kernel launch for the instrumentation.
@@ -1418,13 +1447,8 @@ digest_status digest_partition_create(int64_t n_global, const int64_t *indptr,
                     build_slice_blocks(p->t_rowptr.data(), p->n_own, p->blocks_t_slice);
                 break;
             }
-        p->long_f_gat = build_slice_blocks(p->rowptr.data(), p->n_own, p->blocks_f_gat,
-                                           kGatStrips, kGatMinWork, kGatLong);
-        p->long_tf_gat = build_slice_blocks(p->t_rowptr.data(), p->n_own + p->n_halo,
-                                            p->blocks_tf_gat, kGatStrips, kGatMinWork, kGatLong);
         plan_tiers(*p);
         plan_layout(*p);
-        plan_gat_layout(*p);
         p->gat_done.assign(p->L + 1, 0);
         p->gat_gen.assign(p->L + 1, 0);
         p->gat_act.assign(p->L + 1, 0);
@@ -1523,8 +1547,6 @@ digest_status digest_partition_bind_workspace(digest_partition *p, void *dev_ptr
         {l.blocks_s_rows, p->blocks_s_rows.data(), sizeof(SpmmBlock) * p->blocks_s_rows.size()},
         {l.blocks_t_rows, p->blocks_t_rows.data(), sizeof(SpmmBlock) * p->blocks_t_rows.size()},
         {l.blocks_b, p->blocks_b.data(), sizeof(SpmmBlock) * p->blocks_b.size()},
-        {l.blocks_f_gat, p->blocks_f_gat.data(), sizeof(SpmmBlock) * p->blocks_f_gat.size()},
-        {l.blocks_tf_gat, p->blocks_tf_gat.data(), sizeof(SpmmBlock) * p->blocks_tf_gat.size()},
         {l.blocks_s_slice, p->blocks_s_slice.data(),
          sizeof(SpmmBlock) * p->blocks_s_slice.size()},
         {l.blocks_t_slice, p->blocks_t_slice.data(),
@@ -2451,6 +2473,8 @@ digest_status digest_gat_query(const digest_partition *p, size_t *workspace_byte
 {
     if (!p || !workspace_bytes)
         return fail(DIGEST_EINVAL, "NULL handle or output");
+    if (digest_status st = plan_gat(p))
+        return st;
     *workspace_bytes = p->glay.total;
     return DIGEST_OK;
 }
@@ -2462,11 +2486,23 @@ digest_status digest_gat_bind_workspace(digest_partition *p, void *dev_ptr, size
         return fail(DIGEST_EINVAL, "NULL handle or workspace");
     if ((uintptr_t)dev_ptr % kAlign)
         return fail(DIGEST_EINVAL, "workspace must be %zu-byte aligned", kAlign);
+    if (digest_status st = plan_gat(p))
+        return st;
     if (bytes < p->glay.total)
         return fail(DIGEST_ENOMEM, "GAT workspace has %zu bytes, needs %zu", bytes,
                     p->glay.total);
-    (void)hip_stream;   // nothing is uploaded: every array is written before it is read
-    p->gws = (char *)dev_ptr;
+    // the strips; every other array is written before it is read
+    char *ws = (char *)dev_ptr;
+    for (const auto &u : {std::make_pair(p->glay.blocks_f, &p->blocks_f_gat),
+                          std::make_pair(p->glay.blocks_tf, &p->blocks_tf_gat)})
+        if (!u.second->empty())
+            if (digest_status st = hip_check(
+                    hipMemcpyAsync(ws + u.first, u.second->data(),
+                                   sizeof(SpmmBlock) * u.second->size(), hipMemcpyHostToDevice,
+                                   (hipStream_t)hip_stream),
+                    "GAT upload"))
+                return st;
+    p->gws = ws;
     std::fill(p->gat_done.begin(), p->gat_done.end(), 0);
     return DIGEST_OK;
 }
@@ -2529,7 +2565,8 @@ digest_status digest_gat_forward(digest_partition *p, int32_t layer, const float
         Timed t(p, K_GAT_AGG, layer, s);
         if (digest_status st = hip_check(
                 digest::launch_gat_aggregate(
-                    p->at<SpmmBlock>(strips ? p->lay.blocks_f_gat : p->lay.blocks_f),
+                    strips ? p->gat<SpmmBlock>(p->glay.blocks_f)
+                           : p->at<SpmmBlock>(p->lay.blocks_f),
                     strips ? p->long_f_gat : p->long_f,
                     (int32_t)(strips ? p->blocks_f_gat : p->blocks_f).size(), strips,
                     p->at<int32_t>(p->lay.rowptr), p->at<int32_t>(p->lay.col), alpha, Z, d_out,
@@ -2596,7 +2633,8 @@ digest_status digest_gat_backward(digest_partition *p, int32_t layer, const floa
         Timed t(p, K_GAT_ENTRIES, layer, s);
         if (digest_status st = hip_check(
                 digest::launch_gat_backward(
-                    p->at<SpmmBlock>(strips ? p->lay.blocks_tf_gat : p->lay.blocks_tf),
+                    strips ? p->gat<SpmmBlock>(p->glay.blocks_tf)
+                           : p->at<SpmmBlock>(p->lay.blocks_tf),
                     strips ? p->long_tf_gat : p->long_tf,
                     (int32_t)(strips ? p->blocks_tf_gat : p->blocks_tf).size(), strips,
                     p->at<int32_t>(p->lay.t_rowptr), p->at<int32_t>(p->lay.t_src), S, Z, dO,

@@ -121,3 +121,21 @@ def test_layer_runs_what_its_plan_holds(on_cpu, n, mean, widths, layer, sliced, 
                                  else (0, 0) if want == "dw"
                                  else (sliced, not sliced) if want == "dh_in" else (0, 1)), want
     D.digest_partition_destroy(h)
+
+
+def test_gat_layout_is_planned_by_the_first_call_of_any_thread(on_cpu):
+    """The lists of a dense partition's attention layer are built with the
+    first query, not with the partition, and once."""
+    from concurrent.futures import ThreadPoolExecutor
+    sizes = []
+    for mean in (70, 60):   # strips of rows from 64 entries a row on, and none
+        h = D.digest_partition_create(*partition(2100, mean), (8, 16))
+        with ThreadPoolExecutor(8) as pool:
+            sizes.append(set(pool.map(lambda _: D.digest_gat_query(h), range(32))))
+        nnz = h.nnz
+        sizes[-1] = {s - 4 * nnz for s in sizes[-1]}   # less the weights
+        D.digest_partition_destroy(h)
+    dense, sparse = sizes
+    assert len(dense) == len(sparse) == 1
+    # a 16-byte block per strip (a row or more) and nothing else
+    assert 16 * 2100 / 8 < min(dense) - min(sparse) <= 16 * 2100 + 512
