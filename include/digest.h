@@ -328,9 +328,9 @@ digest_status digest_pull_add(digest_partition *p, int32_t level, float *gstore,
 digest_status digest_gat_query(const digest_partition *p, size_t *workspace_bytes);
 
 /* Bind the GAT workspace (caller-owned device memory, at least the queried
- * size, 256-byte aligned); uploads the work lists of dense partitions on the
- * stream.  Errors: DIGEST_EINVAL, DIGEST_ENOMEM (too small, or host memory),
- * DIGEST_EHIP. */
+ * size, 256-byte aligned); uploads the work lists of dense partitions and
+ * waits for the upload.  Errors: DIGEST_EINVAL, DIGEST_ENOMEM (too small, or
+ * host memory), DIGEST_EHIP. */
 digest_status digest_gat_bind_workspace(digest_partition *p, void *dev_ptr, size_t bytes,
                                         void *hip_stream);
 

@@ -2491,17 +2491,25 @@ digest_status digest_gat_bind_workspace(digest_partition *p, void *dev_ptr, size
     if (bytes < p->glay.total)
         return fail(DIGEST_ENOMEM, "GAT workspace has %zu bytes, needs %zu", bytes,
                     p->glay.total);
-    // the strips; every other array is written before it is read
+    // the strips; every other array is written before it is read.  The layers
+    // may be called on any stream, so the upload is waited for.
     char *ws = (char *)dev_ptr;
+    hipStream_t s = (hipStream_t)hip_stream;
+    bool uploaded = false;
     for (const auto &u : {std::make_pair(p->glay.blocks_f, &p->blocks_f_gat),
                           std::make_pair(p->glay.blocks_tf, &p->blocks_tf_gat)})
-        if (!u.second->empty())
+        if (!u.second->empty()) {
             if (digest_status st = hip_check(
                     hipMemcpyAsync(ws + u.first, u.second->data(),
                                    sizeof(SpmmBlock) * u.second->size(), hipMemcpyHostToDevice,
-                                   (hipStream_t)hip_stream),
+                                   s),
                     "GAT upload"))
                 return st;
+            uploaded = true;
+        }
+    if (uploaded)
+        if (digest_status st = hip_check(hipStreamSynchronize(s), "GAT upload"))
+            return st;
     p->gws = ws;
     std::fill(p->gat_done.begin(), p->gat_done.end(), 0);
     return DIGEST_OK;

@@ -8,7 +8,7 @@
 #include "kernels.h"
 
 namespace {
-int n_sliced = 0, n_whole = 0;
+int n_sliced = 0, n_whole = 0, n_pending = 0;
 constexpr hipError_t kNo = hipErrorNotSupported;
 }  // namespace
 
@@ -19,8 +19,11 @@ void host_kernels_counts(int *sliced, int *whole)
     *sliced = n_sliced, *whole = n_whole;
     n_sliced = n_whole = 0;
 }
+// Copies that no synchronization has followed.
+int host_kernels_pending() { return n_pending; }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t)
 {
+    ++n_pending;
     std::memcpy(d, s, n);
     return hipSuccess;
 }
@@ -36,7 +39,7 @@ hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = nullptr; re
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamGetDevice(hipStream_t, hipDevice_t *d) { *d = 0; return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { n_pending = 0; return hipSuccess; }
 }
 
 namespace digest {

@@ -139,3 +139,17 @@ def test_gat_layout_is_planned_by_the_first_call_of_any_thread(on_cpu):
     assert len(dense) == len(sparse) == 1
     # a 16-byte block per strip (a row or more) and nothing else
     assert 16 * 2100 / 8 < min(dense) - min(sparse) <= 16 * 2100 + 512
+
+
+@pytest.mark.parametrize("mean", [70, 60])   # with strips of rows to upload, and without
+def test_gat_bind_waits_for_its_upload(on_cpu, mean):
+    """The layers may be called on another stream than the bind."""
+    h = D.digest_partition_create(*partition(2100, mean), (8, 16))
+    ws = np.zeros((h.workspace_bytes + D.digest_gat_query(h)) // 4 + 128, np.float32)
+    base = ws.ctypes.data + (-ws.ctypes.data) % 256
+    D._check(on_cpu.digest_partition_bind_workspace(h.handle, base, h.workspace_bytes, None))
+    before = on_cpu.host_kernels_pending()
+    gat = base + -(-h.workspace_bytes // 256) * 256
+    D._check(on_cpu.digest_gat_bind_workspace(h.handle, gat, D.digest_gat_query(h), None))
+    assert on_cpu.host_kernels_pending() == (0 if mean == 70 else before)
+    D.digest_partition_destroy(h)
