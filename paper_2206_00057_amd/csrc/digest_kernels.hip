@@ -2507,15 +2507,16 @@ __global__ __launch_bounds__(256) void k_gat_softmax(int32_t n_rows,
 // The backward's row terms, 16 lanes per owned row i:
 //   D_i  = dh_out_i (masked by h_out_i > 0 with relu)  -> dO_i, zeros past d
 //   c_i  = D_i . h_out_i   (= D_i . o_i: the mask zeroes D where o <= 0)
-//   g2[i][1] = sum_k dpre_ik = (1 - slope) (D_i . op_i - c_i pos_i)
+//   g2[i][1] = sum_k dpre_ik = slope (c_i - c_i) + (1 - slope) (D_i . op_i - c_i pos_i)
 //   rec  = {t_i, maximum, 1 / sum, c_i}, what an entry of row i needs besides
 //          D_i: stored behind it in the same row of dO (columns ld .. ld + 3,
 //          rows ld + 4 apart), so that a gather reads them from its lines
 // The row's sum of score gradients alpha (D . z - c) LeakyReLU' is slope
-// times the sum over all entries, which is c - c = 0, plus (1 - slope) times
-// the sum over the entries of LeakyReLU's positive branch: with op_i the
-// part of o_i from those entries and pos_i their weights (both from the
-// forward) no pass over the entries is needed.
+// times the sum over all entries, which is c - c (0, or NaN where the gradient
+// is not finite), plus (1 - slope) times the sum over the entries of
+// LeakyReLU's positive branch: with op_i the part of o_i from those entries
+// and pos_i their weights (both from the forward) no pass over the entries is
+// needed.
 __global__ __launch_bounds__(256) void k_gat_rows(int32_t n, int32_t d, int32_t ld,
                                                   const float *__restrict__ s,
                                                   const float4 *__restrict__ stat,
@@ -2550,7 +2551,7 @@ __global__ __launch_bounds__(256) void k_gat_rows(int32_t n, int32_t d, int32_t 
         const float4 st = stat[r];
         const float rec[4] = {s[2 * r + 1], st.x, st.y, c};
         store_vec<4>(dO + r * (ld + 4) + ld, rec);
-        g2[2 * r + 1] = (1.f - slope) * (q - c * st.z);
+        g2[2 * r + 1] = slope * (c - c) + (1.f - slope) * (q - c * st.z);
     }
 }
 
@@ -2737,18 +2738,32 @@ k_gat_entries(const SpmmBlock *__restrict__ blocks, int32_t n_long, int32_t n_bl
                         load_vec<4>(g.src + (int64_t)i[u] * g.lds + (cv < dv ? cv : 0) * 4, x[u][ch]);
                     }
                 }
+                // D of an entry past the row's end is dropped: weight 0 alone would
+                // make NaN of an infinite gradient (an infinite z makes its
+                // column NaN whatever the weights)
+                if (BWD && k0 + UE * OF > ke)
+#pragma unroll
+                    for (int u = 0; u < UE; ++u)
+#pragma unroll
+                        for (int ch = 0; ch < NCH; ++ch)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v)
+                                x[u][ch][v] = ok[u] ? x[u][ch][v] : 0.f;
 #pragma unroll
                 for (int u = 0; u < UE; ++u) {
                     if constexpr (BWD) {
                         // (all of rec is loaded here: a part of it that only an entry
                         // in the row uses would be loaded, and waited for, behind ok)
                         asm("" : "+v"(rc[u].x), "+v"(rc[u].y), "+v"(rc[u].z), "+v"(rc[u].w));
-                        float dot = 0.f;   // z is zero past the width
+                        float dot = 0.f;
 #pragma unroll
-                        for (int ch = 0; ch < NCH; ++ch)
+                        for (int ch = 0; ch < NCH; ++ch) {
+                            float to = dot;
 #pragma unroll
                             for (int v = 0; v < 4; ++v)
-                                dot = fmaf(z[ch][v], x[u][ch][v], dot);
+                                to = fmaf(z[ch][v], x[u][ch][v], to);
+                            dot = ch * GL + gl < dv ? to : dot;
+                        }
                         dot = group_sum<GL>(dot);
                         const float pre = rc[u].x + sv;
                         a[u] = ok[u] ? expf(leaky(pre, g.slope) - rc[u].y) * rc[u].z : 0.f;

@@ -82,3 +82,37 @@ def test_diverged_attention_reaches_every_gradient(d):
     ref = c.op.gat_backward(1, x, w, att, dh, dh, oracle.IDENTITY, want_dh_in=True)
     for got, r, name in zip((dw, datt, dx), ref, ("dw", "datt", "dh_in")):
         assert np.isnan(r).all() and torch.isnan(got).all(), name
+
+
+@pytest.mark.parametrize("n,d", [(1200, 7), (1200, 16), (1200, 41), (1200, 61), (1200, 130),
+                                 (1200, 300), (21000, 7), (21000, 61)])
+def test_infinite_gradients_stay_infinite(n, d):
+    """A row whose gradient is infinite, and the last entry of every row of the
+    transpose that names it: infinite and NaN where the oracle's are.  n =
+    21,000: rows in strips."""
+    from paper_2206_00057_amd import digest as D
+    rng = np.random.default_rng(5)
+    mean = 60 if n == 1200 else 70
+    cols = np.sort(rng.integers(0, n - 1, (n, mean)), 1)
+    part = synth.Partition(owned=np.arange(n), halo=np.zeros(0, np.int64),
+                           indptr=np.arange(0, n * mean + 1, mean), indices=cols.reshape(-1),
+                           values=np.ones(n * mean, np.float32))
+    c = Case(n, part, (6, d))
+    assert (c.h.nnz_in >= max(64 * n, 1000000)) == (n == 21000)   # strips
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    x, dh = synth.normal((n, 6), seed=1) - 0.5, synth.normal((n, d), seed=2)
+    w, att = np.abs(synth.normal((6, d), seed=3)), np.abs(synth.normal((d, 2), seed=4)) / d
+    out, dw, datt = (torch.empty(*sh, device="cuda") for sh in ((n, d), (6, d), (d, 2)))
+    dx = torch.empty(n, 6, device="cuda")
+    D.digest_gat_forward(c.h, 1, dev(x), dev(w), dev(att), out, oracle.IDENTITY)
+    h_out = c.op.gat_forward(1, x, w, att, oracle.IDENTITY)
+    f = int(np.argmin(h_out[n - 1]))
+    dh[n - 1, f] = np.inf   # D . z - c: infinite where z > 0 (o < 0), else NaN
+    D.digest_gat_backward(c.h, 1, dev(x), dev(h_out), dev(dh), dev(w), dev(att), dw, datt, dx)
+    ref = c.op.gat_backward(1, x, w, att, h_out, dh, oracle.IDENTITY, want_dh_in=True)
+    for got, r, name in zip((dw, datt, dx), ref, ("dw", "datt", "dh_in")):
+        got, fin = got.cpu().numpy(), np.isfinite(r)
+        np.testing.assert_array_equal(got[~fin], r[~fin], err_msg=name)
+        np.testing.assert_allclose(got[fin], r[fin], rtol=1e-4, err_msg=name,
+                                   atol=1e-4 * np.abs(r[fin]).max(initial=0))
+    assert np.isinf(ref[2]).any() and np.isnan(ref[2][n - 1]).all()
