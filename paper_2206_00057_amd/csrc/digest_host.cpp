@@ -1067,7 +1067,7 @@ const TierPlan *find_tiers(const digest_partition &p, Csr which, int32_t width)
 // (launch_spmm_gemm).  DIGEST_FUSE=0 never fuses, =2 fuses at any size.
 constexpr int64_t kFuseMinRows = 16384;
 
-// The input gradient of a ReLU aggregate-first layer (layer >= 2, 129..256
+// The input gradient of a ReLU aggregate-first layer (layer >= 2, 65..256
 // output floats) runs as P_in^T (D W^T) = (P_in^T D) W^T in one pass over
 // D = dh_out masked by the ReLU derivative (launch_spmm_gemm): the same
 // rules and switch as the fused forward.
@@ -1164,7 +1164,7 @@ digest_status run_spmm(digest_partition *p, Csr which, const float *src0, const 
     const TierPlan *tp = find_tiers(*p, which, d);
     if (tp && !ep && !relu && n_out0 == INT32_MAX && !out1 &&
         (lds == 0 || lds == d) && (out_ld == 0 || out_ld == d) && (out_w == 0 || out_w == d) &&
-        digest::spmm_sliced_ok(d, src0, src1, out)) {
+        digest::spmm_tier_ok(d, src0, src1, out)) {
         // sliced passes over the tiers, then the rest, each adding into out
         const int32_t n_rows = p->n_own;
         const int32_t *trp = p->at<int32_t>(tp->off_rowptr);
@@ -1176,9 +1176,9 @@ digest_status run_spmm(digest_partition *p, Csr which, const float *src0, const 
             const SpmmBlock *b = tblk + tp->blk_off[c];
             const hipError_t e =
                 c < tp->tiers
-                    ? digest::launch_spmm_sliced(b, tp->blk_cnt[c], tp->blk_long[c], rp, tcol,
-                                                 tval, (int64_t)tp->col.size(), src0, src1,
-                                                 n_src0, n_rows, d, out, c > 0, s)
+                    ? digest::launch_spmm_tier(b, tp->blk_cnt[c], tp->blk_long[c], rp, tcol,
+                                               tval, (int64_t)tp->col.size(), src0, src1,
+                                               n_src0, n_rows, d, out, c > 0, s)
                     : digest::launch_spmm(b, tp->blk_cnt[c], tp->blk_long[c], rp, tcol, tval,
                                           src0, src1, n_src0, d, out, s, nullptr, nullptr,
                                           INT32_MAX, false, true);

@@ -3202,7 +3202,7 @@ bool spmm_epilogue_ok(int32_t d, int32_t n2, const float *out2)
            (size_t)d * n2 * sizeof(float) <= 64 * 1024 && ((uintptr_t)out2 % 16) == 0;
 }
 
-bool spmm_sliced_ok(int32_t d, const float *src0, const float *src1, const float *out0)
+bool spmm_tier_ok(int32_t d, const float *src0, const float *src1, const float *out0)
 {
     return d > 0 && pick_vec(d, src0, out0) >= 2 && (!src1 || pick_vec(d, src1, nullptr) >= 2);
 }
@@ -3237,10 +3237,10 @@ hipError_t spmm_tier_t(const SpmmBlock *blocks, int32_t n_long, const int32_t *r
 
 }  // namespace
 
-hipError_t launch_spmm_sliced(const SpmmBlock *blocks, int32_t n_blocks, int32_t n_long,
-                              const int32_t *rowptr, const int32_t *col, const float *val,
-                              int64_t nnz, const float *src0, const float *src1, int32_t n_src0,
-                              int32_t n_rows, int32_t d, float *out0, bool acc, hipStream_t s)
+hipError_t launch_spmm_tier(const SpmmBlock *blocks, int32_t n_blocks, int32_t n_long,
+                            const int32_t *rowptr, const int32_t *col, const float *val,
+                            int64_t nnz, const float *src0, const float *src1, int32_t n_src0,
+                            int32_t n_rows, int32_t d, float *out0, bool acc, hipStream_t s)
 {
     if (n_rows <= 0 || d <= 0)
         return hipSuccess;

@@ -77,13 +77,13 @@ hipError_t launch_spmm(const SpmmBlock *blocks, int32_t n_blocks, int32_t n_long
 // fit one L2 stays resident there).  Needs rows of an even width with 8-byte
 // aligned sources and output (16-byte for float4 gathers).  acc as above.
 constexpr int kSliceFloats = 32;
-bool spmm_sliced_ok(int32_t d, const float *src0, const float *src1, const float *out0);
+bool spmm_tier_ok(int32_t d, const float *src0, const float *src1, const float *out0);
 // The rows are 0 .. n_rows-1 of the CSR; blocks lists its work blocks (the
 // n_long long-row blocks first); nnz >= 1 entries.
-hipError_t launch_spmm_sliced(const SpmmBlock *blocks, int32_t n_blocks, int32_t n_long,
-                              const int32_t *rowptr, const int32_t *col, const float *val,
-                              int64_t nnz, const float *src0, const float *src1, int32_t n_src0,
-                              int32_t n_rows, int32_t d, float *out0, bool acc, hipStream_t s);
+hipError_t launch_spmm_tier(const SpmmBlock *blocks, int32_t n_blocks, int32_t n_long,
+                            const int32_t *rowptr, const int32_t *col, const float *val,
+                            int64_t nnz, const float *src0, const float *src1, int32_t n_src0,
+                            int32_t n_rows, int32_t d, float *out0, bool acc, hipStream_t s);
 
 // Aggregation of the rows named by the blocks out of a source of n_src rows
 // laid out in column slices, [slice][n_src][kSliceFloats] (launch_slice_rows,

@@ -210,10 +210,10 @@ hipError_t launch_dw_narrow(int32_t R, int32_t m0, int32_t F, int32_t N, const f
 }
 
 // what these calls do not reach
-bool spmm_sliced_ok(int32_t, const float *, const float *, const float *) { return false; }
-hipError_t launch_spmm_sliced(const SpmmBlock *, int32_t, int32_t, const int32_t *, const int32_t *,
-                              const float *, int64_t, const float *, const float *, int32_t,
-                              int32_t, int32_t, float *, bool, hipStream_t) { return kNo; }
+bool spmm_tier_ok(int32_t, const float *, const float *, const float *) { return false; }
+hipError_t launch_spmm_tier(const SpmmBlock *, int32_t, int32_t, const int32_t *, const int32_t *,
+                            const float *, int64_t, const float *, const float *, int32_t,
+                            int32_t, int32_t, float *, bool, hipStream_t) { return kNo; }
 bool spmm_gemm_ok(int32_t, int32_t, int32_t, const float *, const float *, const float *,
                   const float *) { return false; }
 hipError_t launch_spmm_gemm(int32_t, const int32_t *, const int32_t *, const float *,
