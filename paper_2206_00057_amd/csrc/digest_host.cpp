@@ -224,20 +224,29 @@ int32_t build_blocks(const std::vector<int32_t> &rowptr, int32_t n_rows,
 }
 
 // Blocks of a sliced aggregation (launch_spmm_slice): rows of more than
-// kSliceLong entries get a workgroup each, the others form strips of
-// consecutive rows with about 1 / kSliceStrips of the CSR's work, a wave
-// each; both by descending entry count, so that the waves of a workgroup end
+// long_row entries get a workgroup each, the others form strips of
+// consecutive rows with about 1 / n_strips of the CSR's work, a wave each;
+// both by descending entry count, so that the waves of a workgroup end
 // together and the longest start first.  Returns the number of long rows.
+// A row is long (long_row 0) from twice a strip's work on, up to kSliceLong
+// entries: a wave with a longer row ends after all others (rows of lognormal
+// length, 2,048 entries for every partition / twice the work, 40 floats,
+// forward, us: 11,250 rows of mean 64 61 / 32, 14,000 of mean 128 62 / 49,
+// 24,000 of mean 64 77 / 55).  Up to 4,096 entries where the strips are that
+// long: 29,125 rows of mean 300 177 / 150, but the Reddit-shaped transpose
+// of 41 floats 244 / 255.
 constexpr int32_t kSliceLong = 2048;
 constexpr int64_t kSliceStrips = 4096;
 constexpr int64_t kSliceRowCost = 32;   // a row's own cost, in entries
 
 int32_t build_slice_blocks(const int32_t *rowptr, int32_t n_rows, std::vector<SpmmBlock> &blocks,
                            int64_t n_strips = kSliceStrips, int64_t min_work = 256,
-                           int32_t long_row = kSliceLong)
+                           int32_t long_row = 0)
 {
     const int64_t total = rowptr[n_rows] - rowptr[0] + kSliceRowCost * n_rows;
     const int64_t target = std::max<int64_t>(min_work, total / n_strips);
+    if (long_row == 0)
+        long_row = (int32_t)std::min<int64_t>(kSliceLong, 2 * target);
     std::vector<SpmmBlock> strips;
     blocks.clear();
     for (int32_t r = 0; r < n_rows;) {
@@ -661,14 +670,26 @@ TfPlan tf_plan(int64_t n_own, int64_t n2, int64_t d_in, int64_t d_out)
 //     floats, lognormal mean 83: 736 / 542); at 150,000 rows they no longer
 //     do (mean 48: 1,108 / 1,229).
 //   entries per row: a slice costs each row its own fixed work, and the
-//     source is laid out once (29,125 rows of 256 floats, mean 8: 105 / 114,
-//     mean 12, Zipf: 215 / 119; 60,000 rows, mean 12: 211 / 250, mean 24,
-//     Zipf: 472 / 284).
-//   source bytes: a source of up to about 6 MB is read out of the L2s anyway
-//     (4,000 rows of 256 floats: 154 / 171, 8,000: 270 / 213).
+//     source is laid out once (rows of lognormal length, 13 entries a row:
+//     24,000 rows of 256 floats 96 / 106, 65,000 237 / 257; 24 entries: 121 /
+//     117 and 329 / 283).
+//   bytes: a source of up to about 6 MB is read out of the L2s anyway (4,000
+//     rows of 256 floats: 154 / 171), and up to 20 MB in part, so that it
+//     takes more entries to pay: 480 MB of gathered rows (14,000 rows of 128
+//     floats: 24 entries a row, 172 MB, 38 / 41, 120 entries 78 / 74; 9,000
+//     of 256: 24 entries 54 / 59, 120 entries 97 / 92).
 //   rows of at most 64 floats: their whole-row kernel is a lane group per
-//     row, which needs more rows and entries to lose (41 floats: 8,000 rows
-//     of mean 625 84 / 71, 29,125 rows of mean 24 26 / 29, mean 32 35 / 32).
+//     row, which needs more rows and entries to lose (40 floats: 8,000 rows
+//     of mean 33, all alike, 24 / 24, mean 128 47 / 37; 14,000 of mean 33
+//     25 / 28, mean 64 28 / 31 and its transpose 59 / 35).  A width that is no
+//     multiple of 4 saves the transpose its padded copy (41 floats: 31 / 27
+//     and 36 / 34 for 40 floats' 24 / 26 and 26 / 32).
+//   width: this is where the measured gain begins on every partition the
+//     other lines let in, not where it ends: 24 to 39 floats gain on large
+//     ones (29,125 rows of mean 360: 32 floats 186 / 144, 36 floats 240 / 239
+//     and the transpose 204 / 158) and lose on small ones (8,100 rows of mean
+//     100: 36 floats 41 / 52, mean 610, the transpose, 80 / 100); 16 floats
+//     lose on both (120 / 139).
 constexpr int64_t kSliceMaxRows = 65536;
 constexpr int32_t kSliceMinWidth = 40;
 
@@ -678,12 +699,11 @@ constexpr int32_t kSliceMinWidth = 40;
 bool sliced_pays(const digest_partition &p, int32_t d)
 {
     const int64_t n = p.n_own;
-    const bool narrow = d <= digest::kNarrowWide;
     if (d < kSliceMinWidth || n > kSliceMaxRows)
         return false;
-    if (narrow ? n < 8000 : n * d * 4 < 6000000)
-        return false;
-    return p.nnz_in >= n * std::max<int64_t>(narrow ? 32 : 12, n / 2500);
+    if (d <= digest::kNarrowWide)
+        return n >= 8000 && p.nnz_in >= n * (d % 4 ? 32 : 48);
+    return n * d * 4 >= 6000000 && p.nnz_in >= 24 * n && (int64_t)p.nnz_in * d * 4 >= 480000000;
 }
 
 // Whether a GAT layer's pass over the entries at width d gives a wave a strip

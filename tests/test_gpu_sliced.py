@@ -16,12 +16,12 @@ pytestmark = pytest.mark.gpu
 
 # owned rows, mean endpoints drawn per row, widths, entries of the longest row
 CASES = [
-    (2504, 9, (600, 602, 48), 0),       # 6.03 MB of 602 floats, about 15 entries a row
+    (2504, 45, (600, 602, 48), 0),      # 6.03 MB of 602 floats
     (4001, 30, (603, 256, 16), 5003),   # odd width, one row over a whole workgroup
-    (8000, 24, (256, 192, 41), 2049),   # last slice of 9 columns, rows of 41 floats
-    (12003, 40, (602, 128, 16), 0),     # a ReLU layer transformed first: D masked as it is laid out
-    (15001, 12, (101, 101, 64), 0),     # scalar loads, one odd row past the strips
-    (16500, 14, (96, 256, 256, 40), 2048),   # above the fused passes' row count
+    (8000, 36, (256, 192, 41), 2049),   # last slice of 9 columns, rows of 41 floats
+    (12003, 46, (602, 128, 16), 0),     # a ReLU layer transformed first: D masked as it is laid out
+    (15001, 45, (101, 101, 64), 0),     # scalar loads, one odd row past the strips
+    (16500, 18, (96, 256, 256, 40), 2048),   # above the fused passes' row count
     # widths below the rule's narrowest that pad to it, no other width sliced
     (10003, 45, (100, 37), 0),
     (9001, 45, (100, 128, 39), 0),
@@ -50,7 +50,7 @@ def test_infinite_rows_stay_infinite(widths):
     from paper_2206_00057_amd import digest as D
     import torch
     n, rng = 8100, np.random.default_rng(3)
-    rows = [np.sort(rng.choice(n - 1, 12 + i % 67, replace=False)) for i in range(n)]
+    rows = [np.sort(rng.choice(n - 1, 31 + i % 67, replace=False)) for i in range(n)]
     rows = [np.concatenate([r, [n - 1] * (i % 3 == 0), [n] * (i % 2)]).astype(np.int64)
             for i, r in enumerate(rows)]
     indptr = np.concatenate([[0], np.cumsum([r.size for r in rows])])

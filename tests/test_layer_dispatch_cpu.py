@@ -61,10 +61,12 @@ CASES = [
     (8100, 34, (100, 37), 1, False),
     (8100, 34, (40, 128, 38), 2, False),      # lists exist, for another width
     (8100, 34, (100, 100, 39), 2, False),
-    (8100, 34, (100, 40), 1, True),
+    (8100, 34, (100, 40), 1, False),          # whole vectors need more entries a row
+    (8100, 50, (100, 40), 1, True),
     (8100, 34, (100, 100, 41), 2, True),
     (7000, 80, (600, 214), 1, False),         # 214 -> 216 crosses 6 MB of rows
     (7000, 80, (600, 215), 1, True),
+    (7000, 79, (600, 215), 1, False),         # just below 480 MB of gathered rows
     (8100, 34, (100, 39, 96), 2, False),      # aggregated first, 39 wide
     (8100, 34, (100, 41, 96), 2, True),
 ]
