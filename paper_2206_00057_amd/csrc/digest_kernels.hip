@@ -2504,7 +2504,7 @@ __global__ __launch_bounds__(256) void k_gat_softmax(int32_t n_rows,
         stat[row] = make_float4(m, inv, pos, 0.f);
 }
 
-// The backward's row terms, 16 lanes per owned row i:
+// The backward's row terms, L lanes per owned row i:
 //   D_i  = dh_out_i (masked by h_out_i > 0 with relu)  -> dO_i, zeros past d
 //   c_i  = D_i . h_out_i   (= D_i . o_i: the mask zeroes D where o <= 0)
 //   g2[i][1] = sum_k dpre_ik = slope (c_i - c_i) + (1 - slope) (D_i . op_i - c_i pos_i)
@@ -2517,6 +2517,7 @@ __global__ __launch_bounds__(256) void k_gat_softmax(int32_t n_rows,
 // LeakyReLU's positive branch: with op_i the part of o_i from those entries
 // and pos_i their weights (both from the forward) no pass over the entries is
 // needed.
+template <int L>
 __global__ __launch_bounds__(256) void k_gat_rows(int32_t n, int32_t d, int32_t ld,
                                                   const float *__restrict__ s,
                                                   const float4 *__restrict__ stat,
@@ -2526,13 +2527,13 @@ __global__ __launch_bounds__(256) void k_gat_rows(int32_t n, int32_t d, int32_t 
                                                   float slope, float *__restrict__ dO,
                                                   float *__restrict__ g2)
 {
-    const int64_t r = (int64_t)blockIdx.x * (256 / 16) + threadIdx.x / 16;
-    const int gl = threadIdx.x % 16;
+    const int64_t r = (int64_t)blockIdx.x * (256 / L) + threadIdx.x / L;
+    const int gl = threadIdx.x % L;
     if (r >= n)
         return;   // whole groups; the sums below stay inside a group
     float c = 0.f, q = 0.f;
 #pragma unroll 4
-    for (int f = gl; f < ld; f += 16) {
+    for (int f = gl; f < ld; f += L) {
         float D = 0.f;
         if (f < d) {
             const float h = h_out[r * d + f];
@@ -2543,7 +2544,7 @@ __global__ __launch_bounds__(256) void k_gat_rows(int32_t n, int32_t d, int32_t 
         dO[r * (ld + 4) + f] = D;
     }
 #pragma unroll
-    for (int off = 8; off > 0; off >>= 1) {
+    for (int off = L / 2; off > 0; off >>= 1) {
         c += __shfl_xor(c, off);
         q += __shfl_xor(q, off);
     }
@@ -2665,6 +2666,16 @@ k_gat_entries(const SpmmBlock *__restrict__ blocks, int32_t n_long, int32_t n_bl
     const bool long_row = wb < n_long;   // uniform
     constexpr int PARTS = MODE == kGatGroups ? GL * SUB * 8 / kWave : 1;   // waves a block
     static_assert(MODE != kGatGroups || (PARTS >= 1 && kSpmmWaves % PARTS == 0), "rows of a wave");
+    // Narrow rows, forward: at the first exchange between a row's groups each
+    // gives one of its two sums for its neighbour's other one, so that from
+    // there on even groups hold out and odd ones op: half the exchanges, which
+    // take as long as the entries on rows of some tens (forward of 100,000 rows
+    // of mean 60, 3 floats: 247 -> 218 us; from 100 floats on no gain, 512
+    // floats 2 us slower).
+    constexpr bool SPLIT = !BWD && GL <= 8;
+    constexpr int HELD = SPLIT ? 1 : ACC;   // sums a group holds then
+    constexpr int HOLD = SPLIT ? 2 : 1;     // groups that hold them
+    static_assert(!SPLIT || (G >= 2 && (MODE != kGatGroups || SUB >= 2)), "a group for each sum");
     const int32_t wi = (wb - n_long) * kSpmmWaves + wave;
     const int32_t bi = long_row || MODE == kGatWaves ? wb : n_long + wi / PARTS;
     if (bi >= n_blocks)
@@ -2798,11 +2809,22 @@ k_gat_entries(const SpmmBlock *__restrict__ blocks, int32_t n_long, int32_t n_bl
         else
             sum_entries(std::integral_constant<int, MODE == kGatGroups ? (U < GL ? U : GL) : U>{},
                         std::integral_constant<int, G>{}, grp);
+        // the groups of a row add up
+        if constexpr (SPLIT) {
+            const bool odd = grp & 1;
 #pragma unroll
-        for (int off = GL; off < kWave; off <<= 1) {   // uniform
+            for (int ch = 0; ch < NCH; ++ch)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float give = odd ? acc[0][ch][v] : acc[1][ch][v];
+                    acc[0][ch][v] = (odd ? acc[1][ch][v] : acc[0][ch][v]) + __shfl_xor(give, GL);
+                }
+        }
+#pragma unroll
+        for (int off = GL * HOLD; off < kWave; off <<= 1) {   // uniform
             if (off < GL * SUB || !own) {
 #pragma unroll
-                for (int c = 0; c < ACC; ++c)
+                for (int c = 0; c < HELD; ++c)
 #pragma unroll
                     for (int ch = 0; ch < NCH; ++ch)
 #pragma unroll
@@ -2812,22 +2834,23 @@ k_gat_entries(const SpmmBlock *__restrict__ blocks, int32_t n_long, int32_t n_bl
                     ds += __shfl_xor(ds, off);
             }
         }
+        const int member = own ? grp % SUB : grp;   // of the row's groups
         if (long_row) {
-            if (grp == 0) {
+            if (member < HOLD) {
 #pragma unroll
-                for (int c = 0; c < ACC; ++c)
+                for (int c = 0; c < HELD; ++c)
 #pragma unroll
                     for (int ch = 0; ch < NCH; ++ch)
-                        store_vec<4>(&red[wave][c * W + (ch * GL + gl) * 4], acc[c][ch]);
-                if (gl == 0)
+                        store_vec<4>(&red[wave][(member + c) * W + (ch * GL + gl) * 4], acc[c][ch]);
+                if (BWD && gl == 0)
                     red[wave][ACC * W] = ds;
             }
             __syncthreads();
-            if (wave != 0 || grp != 0)
+            if (wave != 0 || member >= HOLD)
                 return;
             ds = 0.f;
 #pragma unroll
-            for (int c = 0; c < ACC; ++c)
+            for (int c = 0; c < HELD; ++c)
 #pragma unroll
                 for (int ch = 0; ch < NCH; ++ch)
 #pragma unroll
@@ -2835,22 +2858,23 @@ k_gat_entries(const SpmmBlock *__restrict__ blocks, int32_t n_long, int32_t n_bl
                         acc[c][ch][v] = 0.f;
             for (int w = 0; w < kSpmmWaves; ++w) {
 #pragma unroll
-                for (int c = 0; c < ACC; ++c)
+                for (int c = 0; c < HELD; ++c)
 #pragma unroll
                     for (int ch = 0; ch < NCH; ++ch) {
                         float t[4];
-                        load_vec<4>(&red[w][c * W + (ch * GL + gl) * 4], t);
+                        load_vec<4>(&red[w][(member + c) * W + (ch * GL + gl) * 4], t);
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
                             acc[c][ch][v] += t[v];
                     }
-                ds += red[w][ACC * W];
+                if constexpr (BWD)
+                    ds += red[w][ACC * W];
             }
-        } else if (own ? grp % SUB != 0 : grp != 0) {
+        } else if (member >= HOLD) {
             continue;
         }
-        // one group stores the row; loads are unconditional, so that they
-        // are in flight together
+        // one group stores a row, or each of its sums; loads are unconditional,
+        // so that they are in flight together
         if constexpr (BWD) {
             dt = row < g.n_own ? dt : 0.f;
 #pragma unroll
@@ -2875,6 +2899,10 @@ k_gat_entries(const SpmmBlock *__restrict__ blocks, int32_t n_long, int32_t n_bl
                 const int cv = ch * GL + gl;
                 if (cv >= dv)
                     continue;
+                if (!SPLIT || member == 1)
+                    store_vec<4>(g.op + row * g.ld + cv * 4, acc[HELD - 1][ch]);
+                if (SPLIT && member == 1)
+                    continue;
                 if (g.relu) {
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
@@ -2888,7 +2916,6 @@ k_gat_entries(const SpmmBlock *__restrict__ blocks, int32_t n_long, int32_t n_bl
                         if (cv * 4 + v < g.d)
                             g.out[row * g.d + cv * 4 + v] = acc[0][ch][v];
                 }
-                store_vec<4>(g.op + row * g.ld + cv * 4, acc[ACC - 1][ch]);
             }
         }
     }
@@ -3798,9 +3825,16 @@ hipError_t launch_gat_rows(int32_t n, int32_t d, int32_t ld, const float *s, con
 {
     if (n <= 0)
         return hipSuccess;
-    hipLaunchKernelGGL(k_gat_rows, dim3((unsigned)(((int64_t)n + 15) / 16)), dim3(256), 0, st, n,
-                       d, ld, s, reinterpret_cast<const float4 *>(stat), op, h_out, dh_out, relu,
-                       slope, dO, g2);
+#define DIGEST_GAT_ROWS(L)                                                                      \
+    hipLaunchKernelGGL((k_gat_rows<L>), dim3((unsigned)(((int64_t)n + 256 / L - 1) / (256 / L))), \
+                       dim3(256), 0, st, n, d, ld, s, reinterpret_cast<const float4 *>(stat), op, \
+                       h_out, dh_out, relu, slope, dO, g2)
+    // a wave for a wide row: 16 lanes walk it in a chain of dependent loads
+    if (ld > 64)
+        DIGEST_GAT_ROWS(64);
+    else
+        DIGEST_GAT_ROWS(16);
+#undef DIGEST_GAT_ROWS
     return hipGetLastError();
 }
 
