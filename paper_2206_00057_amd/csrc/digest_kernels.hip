@@ -2510,7 +2510,9 @@ __global__ __launch_bounds__(256) void k_gat_softmax(int32_t n_rows,
 //   g2[i][1] = sum_k dpre_ik = slope (c_i - c_i) + (1 - slope) (D_i . op_i - c_i pos_i)
 //   rec  = {t_i, maximum, 1 / sum, c_i}, what an entry of row i needs besides
 //          D_i: stored behind it in the same row of dO (columns ld .. ld + 3,
-//          rows ld + 4 apart), so that a gather reads them from its lines
+//          rows ld + 4 apart), so that one gather reads both.  Rows of 44
+//          floats stay within two 128-byte lines with them; those of 32, 64,
+//          128 and 256 floats take one line more (nine for eight at 256)
 // The row's sum of score gradients alpha (D . z - c) LeakyReLU' is slope
 // times the sum over all entries, which is c - c (0, or NaN where the gradient
 // is not finite), plus (1 - slope) times the sum over the entries of
@@ -2622,8 +2624,8 @@ struct GatEntries {
 // transposed order and one that summed them are what this replaces:
 // Reddit-shaped layer of 41 floats (14 M entries) 1,347 -> 460 us, its
 // 256-float one 1,967 -> 1,005, Flickr-shaped 256 floats 94 -> 54 (row terms
-// included).  Bound by the gathered lines (the row terms ride in the D row's
-// own) and, on small partitions, by a row's chain of dependent loads.
+// included).  Bound by the gathered lines (up to one of them for the row terms
+// behind D) and, on small partitions, by a row's chain of dependent loads.
 // A lane group of GL lanes holds a row as NCH float4 each and has U entries
 // in flight.  The n_long first blocks are rows whose entries a whole
 // workgroup splits, its waves' sums added in LDS in wave order.  The others,
