@@ -2752,7 +2752,8 @@ k_gat_entries(const SpmmBlock *__restrict__ blocks, int32_t n_long, int32_t n_bl
 #pragma unroll
                     for (int ch = 0; ch < NCH; ++ch) {
                         const int cv = ch * GL + gl;   // past the width: vector 0 again, not used
-                        load_vec<4>(g.src + (int64_t)i[u] * g.lds + (cv < dv ? cv : 0) * 4, x[u][ch]);
+                        load_vec<4>(g.src + (int64_t)i[u] * g.lds + (cv < dv ? cv : 0) * 4,
+                                    x[u][ch]);
                     }
                 }
                 // the next step's ids are requested before this one's rows are used
@@ -3929,8 +3930,8 @@ hipError_t gat_entries(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks
 
 hipError_t launch_gat_aggregate(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks,
                                 bool strips, const int32_t *rowptr, const int32_t *col,
-                                const float *alpha, const float *z, int32_t d, int32_t ld, float *out, bool relu,
-                                float *op, hipStream_t st)
+                                const float *alpha, const float *z, int32_t d, int32_t ld,
+                                float *out, bool relu, float *op, hipStream_t st)
 {
     GatEntries g{};
     g.rowptr = rowptr, g.col = col, g.src = z, g.lds = ld, g.ld = ld, g.d = d;
@@ -3942,8 +3943,8 @@ hipError_t launch_gat_aggregate(const SpmmBlock *blocks, int32_t n_long, int32_t
 hipError_t launch_gat_backward(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks,
                                bool strips, const int32_t *rowptr, const int32_t *col,
                                const float *s, const float *z, const float *dO,
-                               const float *att, int32_t d, int32_t ld, float slope, int32_t n_own, float *g2,
-                               float *dz, hipStream_t st)
+                               const float *att, int32_t d, int32_t ld, float slope,
+                               int32_t n_own, float *g2, float *dz, hipStream_t st)
 {
     GatEntries g{};
     g.rowptr = rowptr, g.col = col, g.src = dO, g.lds = ld + 4, g.ld = ld, g.d = d;

@@ -243,8 +243,8 @@ hipError_t launch_gat_softmax(int32_t n_rows, const int32_t *rowptr, const int32
 // out = act(sum |alpha| z) [rows][d]; op: the part with positive alpha.
 hipError_t launch_gat_aggregate(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks,
                                 bool strips, const int32_t *rowptr, const int32_t *col,
-                                const float *alpha, const float *z, int32_t d, int32_t ld, float *out, bool relu,
-                                float *op, hipStream_t st);
+                                const float *alpha, const float *z, int32_t d, int32_t ld,
+                                float *out, bool relu, float *op, hipStream_t st);
 // The backward's row terms: dO = dh_out (masked by h_out > 0 with relu; its
 // rows are ld + 4 floats apart, the last four for the entries), and g2[i][1]
 // = the row's sum of score gradients.
@@ -256,8 +256,8 @@ hipError_t launch_gat_rows(int32_t n, int32_t d, int32_t ld, const float *s, con
 hipError_t launch_gat_backward(const SpmmBlock *blocks, int32_t n_long, int32_t n_blocks,
                                bool strips, const int32_t *rowptr, const int32_t *col,
                                const float *s, const float *z, const float *dO,
-                               const float *att, int32_t d, int32_t ld, float slope, int32_t n_own, float *g2,
-                               float *dz, hipStream_t st);
+                               const float *att, int32_t d, int32_t ld, float slope,
+                               int32_t n_own, float *g2, float *dz, hipStream_t st);
 
 // GEMM K step; the smallest workgroup tile of C is kGemmBM x kGemmBN.
 constexpr int kGemmBM = 64;
