@@ -579,6 +579,13 @@ __global__ __launch_bounds__(kSpmmThreads) void k_spmm_narrow(
                         load_vec<VEC>(sp + (cv < dv ? cv : 0) * VEC, x[j][u][ch]);
                     }
                 }
+            // Rows of up to 16 floats: no sum before the last gather (exchanges may
+            // move).  Left to itself the compiler saves registers and waits for
+            // gathers one by one (Flickr-shaped layer 2, 8 floats: forward 8.1 us
+            // without this, 6.1 with it, backward 12.3 / 11.1; other widths keep
+            // their gathers together, or lose waves to it).
+            if constexpr (VEC == 4 && GL == 4 && !TWO)
+                __builtin_amdgcn_sched_barrier(0x80 | 0x4);
 #pragma unroll
             for (int j = 0; j < NB; ++j)
 #pragma unroll
