@@ -895,7 +895,7 @@ __device__ __forceinline__ float slice_reduce(const float (&x)[4])
 // ld1) where the row's sum is stored.  The first d columns of a row are
 // stored, relu stores max(x, 0).
 // Bound by the L2s' random 128-byte reads: the Reddit-shaped partition
-// (29,125 rows, 10.4 M entries, 256 floats) gathers 10.6 GB in 535 us, the
+// (29,125 rows, 10.4 M entries, 256 floats) gathers 10.6 GB in 545 us, the
 // layout pass (about 15) included: 20 TB/s, where a bare random gather of
 // such lines reaches 24.  The row-per-wave kernel took 1,161 us: its gathers
 // miss the L2 and are bound by the fabric's 8-9 TB/s.  Three choices matter:
@@ -2629,8 +2629,8 @@ struct GatEntries {
 // value is stored, gathered or transposed.  A pass of its own for the dot
 // products (gathering z rows), one that moved the edge values into
 // transposed order and one that summed them are what this replaces:
-// Reddit-shaped layer of 41 floats (14 M entries) 1,347 -> 460 us, its
-// 256-float one 1,967 -> 1,005, Flickr-shaped 256 floats 94 -> 54 (row terms
+// Reddit-shaped layer of 41 floats (14 M entries) 1,388 -> 393 us, its
+// 256-float one 3,951 -> 1,848, Flickr-shaped 256 floats 88 -> 46 (row terms
 // included).  Bound by the gathered lines (up to one of them for the row terms
 // behind D) and, on small partitions, by a row's chain of dependent loads.
 // A lane group of GL lanes holds a row as NCH float4 each and has U entries
@@ -3864,6 +3864,7 @@ hipError_t launch_gat_rows(int32_t n, int32_t d, int32_t ld, const float *s, con
                        dim3(256), 0, st, n, d, ld, s, reinterpret_cast<const float4 *>(stat), op, \
                        h_out, dh_out, relu, slope, dO, g2)
     // a wave for a wide row: 16 lanes walk it in a chain of dependent loads
+    // (500 rows of 512 floats 18.6 / 5.4 us, 2,000 of 200 10.2 / 6.6)
     if (ld > 64)
         DIGEST_GAT_ROWS(64);
     else
